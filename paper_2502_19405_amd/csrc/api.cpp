@@ -98,6 +98,102 @@ bool elements_disjoint(int64_t b0, int64_t s0, int64_t b1, int64_t s1, int64_t r
 
 repops_status_t hip_status(hipError_t e) { return e == hipSuccess ? REPOPS_OK : REPOPS_ERR_HIP; }
 
+bool tiled_ok(const GemmArgs& g, uint32_t index) {
+  const repops::GemmConfig* c = repops::gemm_tiled_config(static_cast<int>(index));
+  return c && (g.k_block == 0 || g.k_block % c->bk == 0);
+}
+
+bool mfma_ok(const GemmArgs& g, uint32_t index) {
+  const repops::GemmConfig* c = repops::gemm_mfma_config(static_cast<int>(index));
+  return c && g.fused && (g.k_block == 0 || g.k_block % c->bk == 0);
+}
+
+// The launch of a product under REPOPS_LAUNCH_AUTO, and where the split kernels
+// take it (64-deep k blocks, fused order) its estimated time in us (else 0).
+struct GemmChoice {
+  uint32_t kind, index;
+  double us;
+};
+
+GemmChoice choose_gemm(const GemmArgs& g) {
+  // Matrix cores for the fused order (their single-term updates are the fma
+  // chain): with 64-deep k blocks, the entry with the smallest estimated time
+  // among the large tile that suits the product and the kernels that spread the
+  // k blocks over a workgroup's waves; vector tiles for the unfused order; the
+  // simple path for block lengths no tile divides.
+  const int64_t outputs = g.m * g.n * g.batch0 * g.batch1;
+  const int cus = g.fused ? repops::device_cus() : 0;
+  uint32_t pref = 0;  // 128 x 128 tiles, 8 waves, ring
+  double us = 0.0;
+  if (cus > 0 && repops::gemm_split_ok(g, 0)) {
+    auto take = [&](uint32_t index, double t) {
+      if (us <= 0.0 || t < us) {
+        us = t;
+        pref = index;
+      }
+    };
+    if (g.causal == 2) {
+      take(8, repops::gemm_mfma_us(g, 8, cus));  // 64-row tiles
+    } else {
+      // the large tile: staged, register-staged, or (short k) the persistent ring
+      take(0, repops::gemm_mfma_us(g, 0, cus));
+      take(2, repops::gemm_mfma_us(g, 2, cus));
+      int ring_cus = 0;
+      if (g.k <= 256 && repops::gemm_mfma_ring_tiles(g, 9, &ring_cus) > 0)
+        take(9, repops::gemm_mfma_us(g, 9, cus));
+    }
+    const uint32_t first = static_cast<uint32_t>(repops::gemm_mfma_first_split());
+    for (int i = 0; i < repops::gemm_split_count(); ++i)
+      if (repops::gemm_split_ok(g, i)) take(first + static_cast<uint32_t>(i), repops::gemm_split_us(g, i, cus));
+  } else if (outputs <= (int64_t(1) << 20)) {
+    pref = 5;  // small outputs: 64 x 64 tiles
+  } else if (g.k <= 256) {
+    pref = 2;  // short k: register-staged slices
+  } else if (g.causal == 2) {
+    pref = 8;
+  }
+  if (!mfma_ok(g, pref)) pref = 0;
+  if (mfma_ok(g, pref)) return {REPOPS_LAUNCH_GEMM_MFMA, pref, us};
+  const uint32_t tiled = outputs >= (int64_t(1) << 22) ? 1 : 0;
+  if (tiled_ok(g, tiled)) return {REPOPS_LAUNCH_GEMM_TILED, tiled, 0.0};
+  if (tiled_ok(g, 0)) return {REPOPS_LAUNCH_GEMM_TILED, 0, 0.0};
+  return {REPOPS_LAUNCH_GEMM_SIMPLE, 0, 0.0};
+}
+
+// Estimated time in us of a grouped launch: its tiles, longest contraction first,
+// each on the compute unit that is free first.  Units free at the same time are
+// kept together as one span.
+double grouped_us(const repops::GroupArgs& ga, int cus) {
+  struct Span {
+    double free;
+    int64_t units;
+  };
+  Span spans[2 * repops::kMaxGroup + 2] = {{0.0, cus}};
+  int count = 1;
+  for (int p = 0; p < ga.count; ++p) {
+    int64_t tiles = ga.first[p + 1] - ga.first[p];
+    const double us = 4.0 * static_cast<double>((ga.g[p].k + 63) / 64) + 6.2;
+    for (int i = 0; i < count; ++i) spans[i].free += us * static_cast<double>(tiles / cus);
+    tiles %= cus;
+    for (int i = 0; i < count && tiles > 0; ++i) {  // spans in order of `free`
+      const int64_t n = tiles < spans[i].units ? tiles : spans[i].units;
+      if (n < spans[i].units) {
+        for (int j = count++; j > i + 1; --j) spans[j] = spans[j - 1];
+        spans[i + 1] = {spans[i].free, spans[i].units - n};
+      }
+      spans[i] = {spans[i].free + us, n};
+      tiles -= n;
+    }
+    for (int i = 1; i < count; ++i)
+      for (int j = i; j > 0 && spans[j].free < spans[j - 1].free; --j) {
+        const Span t = spans[j];
+        spans[j] = spans[j - 1];
+        spans[j - 1] = t;
+      }
+  }
+  return 2.7 + spans[count - 1].free;
+}
+
 repops_status_t run_gemm(const repops_order_t* order, GemmArgs& g, const repops_launch_t* launch,
                          hipStream_t stream) {
   if (!order_valid(order)) return REPOPS_ERR_ORDER;
@@ -116,51 +212,18 @@ repops_status_t run_gemm(const repops_order_t* order, GemmArgs& g, const repops_
       return REPOPS_ERR_LAUNCH;
     }
   }
-  auto tiled_ok = [&](const repops::GemmConfig* c) {
-    return c && (g.k_block == 0 || g.k_block % c->bk == 0);
-  };
-  auto mfma_ok = [&](const repops::GemmConfig* c) {
-    return c && g.fused && (g.k_block == 0 || g.k_block % c->bk == 0);
-  };
   if (kind == REPOPS_LAUNCH_AUTO) {
-    // Matrix cores for the fused order (their single-term updates are the fma
-    // chain), the large tile for big outputs; vector tiles for the unfused
-    // order; the simple path for block lengths no tile divides.
-    const int64_t outputs = g.m * g.n * g.batch0 * g.batch1;
-    int mfma_pref = 0;                                  // 128 x 128 tiles, 8 waves, ring
-    if (outputs <= (int64_t(1) << 20)) {
-      mfma_pref = 5;                                    // small outputs: 64 x 64 tiles
-    } else if (g.k <= 256) {
-      // short k: the persistent ring form where each compute unit takes at
-      // least four tiles in turn, else register-staged slices
-      int cus = 0;
-      const int64_t ring = repops::gemm_mfma_ring_tiles(g, 9, &cus);
-      mfma_pref = cus > 0 && ring >= 4 * static_cast<int64_t>(cus) ? 9 : 2;
-    } else if (g.causal == 2) {
-      mfma_pref = 8;                                    // causal A: 64-row tiles
-    }
-    if (!mfma_ok(repops::gemm_mfma_config(mfma_pref))) mfma_pref = 0;
-    const int tiled_pref = outputs >= (int64_t(1) << 22) ? 1 : 0;
-    if (mfma_ok(repops::gemm_mfma_config(mfma_pref))) {
-      kind = REPOPS_LAUNCH_GEMM_MFMA;
-      index = mfma_pref;
-    } else if (tiled_ok(repops::gemm_tiled_config(tiled_pref))) {
-      kind = REPOPS_LAUNCH_GEMM_TILED;
-      index = tiled_pref;
-    } else if (tiled_ok(repops::gemm_tiled_config(0))) {
-      kind = REPOPS_LAUNCH_GEMM_TILED;
-      index = 0;
-    } else {
-      kind = REPOPS_LAUNCH_GEMM_SIMPLE;
-    }
+    const GemmChoice c = choose_gemm(g);
+    kind = c.kind;
+    index = c.index;
   }
   if (kind == REPOPS_LAUNCH_GEMM_SIMPLE) return hip_status(repops::launch_gemm_simple(g, stream));
   if (kind == REPOPS_LAUNCH_GEMM_TILED) {
-    if (!tiled_ok(repops::gemm_tiled_config(static_cast<int>(index)))) return REPOPS_ERR_LAUNCH;
+    if (!tiled_ok(g, index)) return REPOPS_ERR_LAUNCH;
     return hip_status(repops::launch_gemm_tiled(g, static_cast<int>(index), stream));
   }
   // matrix-core path
-  if (!mfma_ok(repops::gemm_mfma_config(static_cast<int>(index)))) return REPOPS_ERR_LAUNCH;
+  if (!mfma_ok(g, index)) return REPOPS_ERR_LAUNCH;
   return hip_status(repops::launch_gemm_mfma(g, static_cast<int>(index), stream));
 }
 
@@ -543,14 +606,15 @@ repops_status_t repops_matmul_grouped(const repops_order_t* order, int32_t count
     one = one && g[p].k > 0 && repops::gemm_mfma_staged_ok(g[p], 0);
   }
   if (n_live == 0) return REPOPS_OK;
-  if (!one) {
+  auto one_by_one = [&]() -> repops_status_t {
     for (int p = 0; p < count; ++p) {
       if (!live[p]) continue;
       const repops_status_t st = run_gemm(order, g[p], nullptr, s);
       if (st != REPOPS_OK) return st;
     }
     return REPOPS_OK;
-  }
+  };
+  if (!one) return one_by_one();
   // One launch: the products with the longest contraction first, so that
   // their tiles start first and the short ones fill the compute units behind
   // them.
@@ -573,6 +637,16 @@ repops_status_t repops_matmul_grouped(const repops_order_t* order, int32_t count
     ga.first[i + 1] = ga.first[i] + ga.tiles_m[i] * ga.tiles_n[i];
   }
   if (ga.first[n] > kMaxDim) return REPOPS_ERR_SHAPE;
+  // One by one where the products' own launches are estimated faster by more
+  // than the estimates' scatter: few tokens, whose tiles leave most units idle.
+  const int cus = repops::device_cus();
+  double alone = 0.0;
+  for (int i = 0; i < n && cus > 0; ++i) {
+    const double us = choose_gemm(ga.g[i]).us;
+    if (us <= 0.0) alone = INFINITY;  // not estimated
+    alone += us;
+  }
+  if (cus > 0 && alone < 0.88 * grouped_us(ga, cus)) return one_by_one();
   return hip_status(repops::launch_gemm_mfma_grouped(ga, s));
 }
 

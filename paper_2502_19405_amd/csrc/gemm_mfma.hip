@@ -21,7 +21,10 @@
 // block starts from +0.
 #include <hip/hip_runtime.h>
 
+#include <cmath>
+
 #include "gemm_store.h"
+#include "gemm_tiles.h"
 #include "repops_internal.h"
 
 #pragma clang fp contract(off)
@@ -30,80 +33,6 @@ namespace repops {
 namespace {
 
 typedef float v32f __attribute__((ext_vector_type(32)));
-
-// Map the launch-order tile index so that the tiles one XCD receives (the
-// hardware deals workgroups round-robin over 8 XCDs) form a compact panel of
-// GROUP_M tile rows, which share A and B slices in that XCD's L2.
-__device__ __forceinline__ void tile_coords(int64_t t, int64_t ntiles, int64_t tiles_m,
-                                            int64_t tiles_n, int64_t* bz, int64_t* tm,
-                                            int64_t* tn) {
-  constexpr int64_t kXcd = 8, kGroupM = 4;
-  if (ntiles % kXcd == 0) t = (t % kXcd) * (ntiles / kXcd) + t / kXcd;
-  const int64_t per_batch = tiles_m * tiles_n;
-  *bz = t / per_batch;
-  const int64_t r = t % per_batch;
-  const int64_t group = r / (kGroupM * tiles_n);
-  const int64_t first_m = group * kGroupM;
-  const int64_t gsize = (tiles_m - first_m) < kGroupM ? (tiles_m - first_m) : kGroupM;
-  const int64_t in_group = r % (kGroupM * tiles_n);
-  *tm = first_m + in_group % gsize;
-  *tn = in_group / gsize;
-}
-
-// Causal products (per batch element, row i, column j, contraction index kk).
-// causal == 1: only outputs with j <= i are wanted, so a tile whose first
-// column lies past its last row is skipped (its outputs are left unwritten).
-// causal == 2: A is zero at kk > i, so a row tile starting at m0 needs k only
-// up to the end of the k block holding row m0 + bm - 1's diagonal; every later
-// block is a chain of zero products, whose partial is +0 and leaves acc
-// unchanged (acc + (+0) = acc; acc is never -0), so skipping it keeps the bits.
-__device__ __forceinline__ bool tile_above_diagonal(const GemmArgs& g, int64_t m0, int bm,
-                                                    int64_t n0) {
-  return g.causal == 1 && n0 > m0 + bm - 1;
-}
-
-__device__ __forceinline__ int64_t k_extent(const GemmArgs& g, int64_t m0, int bm) {
-  if (g.causal != 2 || g.k_block <= 0) return g.k;
-  const int64_t end = (m0 + bm + g.k_block - 1) / g.k_block * g.k_block;
-  return end < g.k ? end : g.k;
-}
-
-// With causal == 1, square tiles and at least as many tile columns as rows,
-// the launch covers only the tiles at or below each batch element's diagonal
-// (tn <= tm): tile r of a batch element is the r-th of the lower triangle in
-// row order.
-__device__ __host__ __forceinline__ bool causal_triangle(int causal, int bm, int bn,
-                                                         int64_t tiles_m, int64_t tiles_n) {
-  return causal == 1 && bm == bn && tiles_n >= tiles_m;
-}
-
-// Tile of launch index t for any product: the lower triangle's tiles only (see
-// causal_triangle), or every tile with tile_coords -- row tiles in reverse order
-// when A is zero above its diagonal (causal == 2), so that the row tiles with
-// the longest contraction start first.
-__device__ __forceinline__ void tile_of(const GemmArgs& g, int bm, int bn, int64_t t,
-                                        int64_t ntiles, int64_t tiles_m, int64_t tiles_n,
-                                        int64_t* bz, int64_t* tm, int64_t* tn) {
-  if (causal_triangle(g.causal, bm, bn, tiles_m, tiles_n)) {
-    constexpr int64_t kXcd = 8;
-    if (ntiles % kXcd == 0) t = (t % kXcd) * (ntiles / kXcd) + t / kXcd;
-    const int64_t per = tiles_m * (tiles_m + 1) / 2;
-    *bz = t / per;
-    const int64_t r = t % per;
-    // the last row tile whose triangle starts at or before r (integer
-    // bisection; r < per, so it lies below tiles_m)
-    int64_t row = 0, hi = tiles_m - 1;
-    while (row < hi) {
-      const int64_t mid = (row + hi + 1) / 2;
-      if (mid * (mid + 1) / 2 <= r) row = mid; else hi = mid - 1;
-    }
-    *tm = row;
-    *tn = r - row * (row + 1) / 2;
-    return;
-  }
-  tile_coords(t, ntiles, tiles_m, tiles_n, bz, tm, tn);
-  if (g.causal == 2) *tm = tiles_m - 1 - *tm;
-}
 
 template <int BM, int BN, int BK, int WM, int WN, bool TA, bool TB>
 struct MfmaTile {
@@ -324,10 +253,9 @@ __global__ __launch_bounds__(64 * WM * WN, MINW) void gemm_mfma_kernel(GemmArgs 
 //   k-major:  [16 k][rows]: a lane reads one value per k (transposed A;
 //     row-major B), two k at once with a paired read.
 // Rows past M (columns past N) are loaded from the last valid row (column):
-// they only feed outputs that are never stored.  K must be a multiple of BK,
-// rows 16-byte aligned and the k-major operand's row count (N of row-major B,
-// M of transposed A) a multiple of 4; otherwise the register-staged kernel of
-// the same tile shape runs.
+// they only feed outputs that are never stored.  Which products the staged
+// kernels take is gemm_mfma_staged_ok's; the others run the register-staged
+// kernel of the same tile shape.
 //
 // Pipelining (a wave may be the only one on its SIMD, so whatever it does
 // between two matrix steps idles the matrix unit unless it fits inside the
@@ -627,8 +555,9 @@ struct StagedTile {
   // 0 .. NS - 1 and pk[0] the first group of slice 0.  acc receives the tile's
   // accumulators; past the last slice the ring is refilled from nsrc (see
   // slice), and pk[0] then holds the first group of that tile's slice 0.
+  // nload >= nslices: slices the ring loads (a short last block's follow).
   __device__ static void dual_fast(Smem& sm, const Src& src, const Src& nsrc, int nlim,
-                                   int nslices, int lane, int wave, int wm0, int wn0,
+                                   int nslices, int nload, int lane, int wave, int wm0, int wn0,
                                    Pack (&pk)[2], v32f (&acc)[IM][IN]) {
     // Q starts at +0, so the first block adds +0 to +0.
     v32f P[IM][IN], Q[IM][IN];
@@ -642,11 +571,11 @@ struct StagedTile {
       }
     int s0 = 0;
     for (; s0 + 2 * NS <= nslices; s0 += 2 * NS) {
-      turn(sm, src, nsrc, nlim, s0, nslices, lane, wave, wm0, wn0, pk, P, acc, Q);
-      turn(sm, src, nsrc, nlim, s0 + NS, nslices, lane, wave, wm0, wn0, pk, Q, acc, P);
+      turn(sm, src, nsrc, nlim, s0, nload, lane, wave, wm0, wn0, pk, P, acc, Q);
+      turn(sm, src, nsrc, nlim, s0 + NS, nload, lane, wave, wm0, wn0, pk, Q, acc, P);
     }
     if (s0 < nslices) {
-      turn(sm, src, nsrc, nlim, s0, nslices, lane, wave, wm0, wn0, pk, P, acc, Q);
+      turn(sm, src, nsrc, nlim, s0, nload, lane, wave, wm0, wn0, pk, P, acc, Q);
 #pragma unroll
       for (int i = 0; i < IM; ++i)
 #pragma unroll
@@ -657,6 +586,72 @@ struct StagedTile {
 #pragma unroll
         for (int j = 0; j < IN; ++j) acc[i][j] = acc[i][j] + Q[i][j];
     }
+  }
+
+  // A tile whose contraction may end inside a block or a slice (64-deep blocks
+  // of one ring turn, the second partial set): the end of it runs by itself
+  // behind the ring turns: its whole slices are in the ring by then, and a cut
+  // slice costs one memory round trip per tile.  (Products whose K is no multiple
+  // of 64 took the loop without unrolled turns, and with K no multiple of 16 the
+  // register-staged kernel: 2000^3 212 against 136 us for 2048^3; weight
+  // gradients of 1389 tokens, 4096 x 4096 outputs, 711 -> 391 us.)
+  static constexpr bool CUT = DUAL && BK <= 64 && 64 / BK == NS;
+
+  // Slice s, which K cuts short, into ring slot: k rows (k groups of 4) past the
+  // end repeat the last one, which is in bounds; no step reads them.
+  __device__ static void issue_cut(Smem& sm, const Src& src, int s, int K, int slot, int wave,
+                                   int lane) {
+    const int k0 = s * BK;
+    auto back = [&](bool packed, int rows, int t) {
+      const int k = k0 + (packed ? 4 * (t / (rows / 64)) : (t * 256 + lane * 4) / rows);
+      const int last = packed ? K - 4 : K - 1;
+      return k > last ? k - last : 0;
+    };
+#pragma unroll
+    for (int u = 0; u < AU; ++u) {
+      const int t = wave + u * NW;
+      __builtin_amdgcn_global_load_lds(
+          (global_void_ptr)(src.a[u] + (k0 - back(!TA, BM, t)) * src.astep),
+          (lds_void_ptr)(sm.a[slot] + t * 256), 16, 0, 0);
+    }
+#pragma unroll
+    for (int u = 0; u < BU; ++u) {
+      const int t = wave + u * NW;
+      __builtin_amdgcn_global_load_lds(
+          (global_void_ptr)(src.b[u] + (k0 - back(TB, BN, t)) * src.bstep),
+          (lds_void_ptr)(sm.b[slot] + t * 256), 16, 0, 0);
+    }
+  }
+
+  // The k indices behind the first `fast` slices (fewer than a block): the whole
+  // slices among them are in the ring already, slots 0 and on.
+  __device__ static void last_block(Smem& sm, const Src& src, int K, int fast, int nslices,
+                                    int lane, int wave, int wm0, int wn0, v32f (&P)[IM][IN],
+                                    v32f (&acc)[IM][IN]) {
+    const int left = K - fast * BK;  // uniform, below 64
+    const int slot = nslices - fast;
+    if (nslices * BK < K) issue_cut(sm, src, nslices, K, slot, wave, lane);
+    wait_vmcnt<0>();  // also the re-loads past the end
+    if (left == 0) return;
+    __syncthreads();
+    Pack pk;
+    for (int k = 0; k < left; k += 4) {
+      const int s = k / BK;
+      read_pack(sm.a[s], sm.b[s], lane, wm0, wn0, k % BK / 4, pk);
+#pragma unroll
+      for (int c = 0; c < 4; ++c) {
+        if (k + c >= left) break;
+#pragma unroll
+        for (int i = 0; i < IM; ++i)
+#pragma unroll
+          for (int j = 0; j < IN; ++j)
+            P[i][j] = __builtin_amdgcn_mfma_f32_32x32x1f32(pk.a[i][c], pk.b[j][c], P[i][j], 0, 0, 0);
+      }
+    }
+#pragma unroll
+    for (int i = 0; i < IM; ++i)
+#pragma unroll
+      for (int j = 0; j < IN; ++j) acc[i][j] = acc[i][j] + P[i][j];
   }
 
   // Accumulator layout (lane l, register r): block r / 16 holds columns
@@ -777,20 +772,18 @@ struct StagedTile {
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);  // uniform in the wave
     const int wm0 = (wave / WN) * TWM;
     const int wn0 = (wave % WN) * TWN;
-    // the host guarantees K / BK and k_block / BK fit in int
-    const int nslices = static_cast<int>(k_extent(g, m0, BM) / BK);
+    // the host guarantees K / BK and k_block / BK fit in int; nslices: whole slices
+    const int64_t K = k_extent(g, m0, BM);
+    const int nslices = static_cast<int>(K / BK);
     const int spb = g.k_block > 0 ? static_cast<int>(g.k_block / BK) : (nslices > 0 ? nslices : 1);
     const Src src = sources(g, g.A + b0 * g.sa0 + b1 * g.sa1, g.B + b0 * g.sb0 + b1 * g.sb1, m0,
                             n0, wave, lane);
 
-    v32f P[IM][IN], acc[IM][IN];
+    v32f acc[IM][IN];
 #pragma unroll
     for (int i = 0; i < IM; ++i)
 #pragma unroll
-      for (int j = 0; j < IN; ++j) {
-        P[i][j] = v32f{};
-        acc[i][j] = v32f{};
-      }
+      for (int j = 0; j < IN; ++j) acc[i][j] = v32f{};
     // Prologue: the ring's NS slots filled with slices 0 .. NS - 1; slice 0
     // published and its first group read.
     Pack pk[2];
@@ -806,28 +799,31 @@ struct StagedTile {
     // whole number of ring turns: one loop iteration is one turn, with the
     // ring slots and the block boundaries known at compile time.
     constexpr int FSPB = BK <= 64 ? 64 / BK : 0;
-    if (FSPB > 0 && NS % FSPB == 0 && spb == FSPB && nslices % NS == 0) {
-      if constexpr (DUAL && FSPB == NS) {
+    v32f P[IM][IN] = {};
+    if (CUT && spb == FSPB) {
+      if constexpr (CUT) {
         // The second partial set: one ring turn is one k block, alternating
         // between P and Q, and each block's partials join acc during the next
         // block's first slice.
-        dual_fast(sm, src, src, nslices - 1, nslices, lane, wave, wm0, wn0, pk, acc);
-      } else {
-        for (int s0 = 0; s0 < nslices; s0 += NS) {
+        const int fast = nslices / NS * NS;
+        dual_fast(sm, src, src, nslices - 1, fast, nslices, lane, wave, wm0, wn0, pk, acc);
+        last_block(sm, src, static_cast<int>(K), fast, nslices, lane, wave, wm0, wn0, P, acc);
+      }
+    } else if (FSPB > 0 && NS % FSPB == 0 && spb == FSPB && nslices % NS == 0) {
+      for (int s0 = 0; s0 < nslices; s0 += NS) {
 #pragma unroll
-          for (int t = 0; t < NS; ++t) {
-            if (t % FSPB == 0)
-              slice<true, true>(sm, src, src, nslices - 1, s0 + t, nslices, t, (t + 1) % NS,
-                                lane, wave, wm0, wn0, pk, P, acc, P);
-            else
-              slice<false, true>(sm, src, src, nslices - 1, s0 + t, nslices, t, (t + 1) % NS,
-                                 lane, wave, wm0, wn0, pk, P, acc, P);
-            if (t % FSPB == FSPB - 1) {
+        for (int t = 0; t < NS; ++t) {
+          if (t % FSPB == 0)
+            slice<true, true>(sm, src, src, nslices - 1, s0 + t, nslices, t, (t + 1) % NS, lane,
+                              wave, wm0, wn0, pk, P, acc, P);
+          else
+            slice<false, true>(sm, src, src, nslices - 1, s0 + t, nslices, t, (t + 1) % NS, lane,
+                               wave, wm0, wn0, pk, P, acc, P);
+          if (t % FSPB == FSPB - 1) {
 #pragma unroll
-              for (int i = 0; i < IM; ++i)
+            for (int i = 0; i < IM; ++i)
 #pragma unroll
-                for (int j = 0; j < IN; ++j) acc[i][j] = acc[i][j] + P[i][j];
-            }
+              for (int j = 0; j < IN; ++j) acc[i][j] = acc[i][j] + P[i][j];
           }
         }
       }
@@ -914,7 +910,7 @@ struct StagedTile {
       if (more) locate(g, tn, ntiles, tiles_m, tiles_n, &nb0, &nb1, &nm0, &nn0);
       const Src nsrc = more ? sources_of(g, nb0, nb1, nm0, nn0, wave, lane) : src;
       v32f acc[IM][IN];
-      dual_fast(sm, src, nsrc, nslices - 1, nslices, lane, wave, wm0, wn0, pk, acc);
+      dual_fast(sm, src, nsrc, nslices - 1, nslices, nslices, lane, wave, wm0, wn0, pk, acc);
       store_tile(g, b0, b1, m0, n0, lane, wm0, wn0, acc);
       if (!more) break;
       t = tn;
@@ -984,6 +980,7 @@ __global__ __launch_bounds__(64 * WM * WN, MINW) void gemm_mfma_grouped_kernel(G
 struct MfmaEntry {
   GemmConfig cfg;
   int threads;
+  bool cut;  // the staged kernels run a short last block (StagedTile::CUT)
   void (*kernel[4])(GemmArgs, int64_t, int64_t, int64_t, int);  // [ta * 2 + tb]
   // staged variant of the same tile shape (nullptr: none); needs K % 16 == 0
   // and 16-byte aligned rows.  [0]: for products with no scale, bias or GELU
@@ -997,7 +994,7 @@ struct MfmaEntry {
 // MINW: waves per SIMD the register allocation must leave room for.
 #define REPOPS_MFMA(BM, BN, BK, WM, WN, MINW)                                                 \
   {{#BM "x" #BN "x" #BK "/w" #WM "x" #WN "/o" #MINW, BM, BN, BK},                             \
-   64 * WM * WN,                                                                              \
+   64 * WM * WN, false,                                                                       \
    {gemm_mfma_kernel<BM, BN, BK, WM, WN, MINW, false, false>,                                 \
     gemm_mfma_kernel<BM, BN, BK, WM, WN, MINW, false, true>,                                  \
     gemm_mfma_kernel<BM, BN, BK, WM, WN, MINW, true, false>,                                  \
@@ -1023,7 +1020,8 @@ struct MfmaEntry {
 // waves, each owning whole 64 x 32 instruction tiles).
 #define REPOPS_STAGED(BM, BN, BK, WM, WN, NS, MINW, FWM, FWN, EPI0)                          \
   {{#BM "x" #BN "x" #BK "/w" #WM "x" #WN "/o" #MINW "/s" #NS, BM, BN, BK},                    \
-   64 * WM * WN,                                                                              \
+   64 * WM * WN, StagedTile<BM, BN, BK, WM, WN, NS, false, false,                             \
+                            (BM / WM / 32) * (BN / WN / 64) == 1>::CUT,                       \
    {gemm_mfma_kernel<BM, BN, BK, FWM, FWN, MINW, false, false>,                               \
     gemm_mfma_kernel<BM, BN, BK, FWM, FWN, MINW, false, true>,                                \
     gemm_mfma_kernel<BM, BN, BK, FWM, FWN, MINW, true, false>,                                \
@@ -1035,7 +1033,8 @@ struct MfmaEntry {
 // per wave: the second partial set).
 #define REPOPS_RING(BM, BN, BK, WM, WN, NS, MINW, FWM, FWN)                                  \
   {{#BM "x" #BN "x" #BK "/w" #WM "x" #WN "/o" #MINW "/s" #NS "/ring", BM, BN, BK},            \
-   64 * WM * WN,                                                                              \
+   64 * WM * WN, StagedTile<BM, BN, BK, WM, WN, NS, false, false,                             \
+                            (BM / WM / 32) * (BN / WN / 64) == 1>::CUT,                       \
    {gemm_mfma_kernel<BM, BN, BK, FWM, FWN, MINW, false, false>,                               \
     gemm_mfma_kernel<BM, BN, BK, FWM, FWN, MINW, false, true>,                                \
     gemm_mfma_kernel<BM, BN, BK, FWM, FWN, MINW, true, false>,                                \
@@ -1064,21 +1063,42 @@ const MfmaEntry kMfma[] = {
 };
 constexpr int kMfmaCount = sizeof(kMfma) / sizeof(kMfma[0]);
 
-bool aligned16(const void* p) { return reinterpret_cast<uintptr_t>(p) % 16 == 0; }
+// 16-byte aligned rows and batch origins of both operands.
+bool operands_aligned(const GemmArgs& g) {
+  auto aligned = [](const float* p, int64_t ld, int64_t s0, int64_t s1) {
+    return reinterpret_cast<uintptr_t>(p) % 16 == 0 && ld % 4 == 0 && s0 % 4 == 0 && s1 % 4 == 0;
+  };
+  return aligned(g.A, g.lda, g.sa0, g.sa1) && aligned(g.B, g.ldb, g.sb0, g.sb1);
+}
 
 }  // namespace
 
-int gemm_mfma_count() { return kMfmaCount; }
+int gemm_mfma_count() { return kMfmaCount + gemm_split_count(); }
 const GemmConfig* gemm_mfma_config(int index) {
-  return (index >= 0 && index < kMfmaCount) ? &kMfma[index].cfg : nullptr;
+  if (index >= kMfmaCount) return gemm_split_config(index - kMfmaCount);
+  return index >= 0 ? &kMfma[index].cfg : nullptr;
 }
 
+// Whether the staged kernels of entry `index` take this product: 16-byte aligned
+// rows, operands stored along rows with a multiple of 4 of them, and whole k
+// slices -- or, with 64-deep k blocks on the entries that run a short last block
+// (StagedTile::CUT), any K whose operands stored along k have a multiple of 4.
 bool gemm_mfma_staged_ok(const GemmArgs& g, int index) {
   const MfmaEntry& e = kMfma[index];
-  const bool vec_ok = aligned16(g.A) && g.lda % 4 == 0 && g.sa0 % 4 == 0 && g.sa1 % 4 == 0 &&
-                      aligned16(g.B) && g.ldb % 4 == 0 && g.sb0 % 4 == 0 && g.sb1 % 4 == 0;
-  return e.staged[1][0] && vec_ok && g.k % e.cfg.bk == 0 && g.k / e.cfg.bk <= INT32_MAX &&
-         g.k_block / e.cfg.bk <= INT32_MAX && (!g.ta || g.m % 4 == 0) && (g.tb || g.n % 4 == 0);
+  if (!e.staged[1][0] || !operands_aligned(g) || (g.ta && g.m % 4 != 0) ||
+      (!g.tb && g.n % 4 != 0) || g.k / e.cfg.bk > INT32_MAX / 64 ||
+      g.k_block / e.cfg.bk > INT32_MAX)
+    return false;
+  if (g.k % e.cfg.bk == 0) return true;
+  return e.cut && g.k_block == 64 && ((g.ta && !g.tb) || g.k % 4 == 0);
+}
+
+int device_cus() {
+  int dev = 0, cus = 0;
+  if (hipGetDevice(&dev) != hipSuccess ||
+      hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
+    return 0;
+  return cus > 0 ? cus : 0;
 }
 
 // Tiles of a launch that the ring form of entry `index` can take, else 0: every
@@ -1096,15 +1116,40 @@ int64_t gemm_mfma_ring_tiles(const GemmArgs& g, int index, int* cus) {
   const int64_t tiles_n = (g.n + e.cfg.bn - 1) / e.cfg.bn;
   const bool tri = causal_triangle(g.causal, e.cfg.bm, e.cfg.bn, tiles_m, tiles_n);
   if (g.causal != 0 && !tri) return 0;
-  int dev = 0;
-  if (hipGetDevice(&dev) != hipSuccess ||
-      hipDeviceGetAttribute(cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
-      *cus <= 0) {
-    *cus = 0;
-    return 0;
-  }
+  *cus = device_cus();
+  if (*cus == 0) return 0;
   const int64_t per_batch = tri ? tiles_m * (tiles_m + 1) / 2 : tiles_m * tiles_n;
   return per_batch * g.batch0 * g.batch1;
+}
+
+int gemm_mfma_first_split() { return kMfmaCount; }
+
+// Measured as the split entries' estimates were: us per tile's k block and per
+// tile of one round of tiles over the compute units, for the staged (or ring)
+// kernel and for the register-staged one that takes its place at sizes or
+// alignments the staged kernel declines.  Entry 8 has three tiles per compute
+// unit under way, so its rounds do not step.
+double gemm_mfma_us(const GemmArgs& g, int index, int cus) {
+  const MfmaEntry& e = kMfma[index];
+  const bool staged = gemm_mfma_staged_ok(g, index);
+  const int64_t tiles_m = (g.m + e.cfg.bm - 1) / e.cfg.bm;
+  const int64_t tiles_n = (g.n + e.cfg.bn - 1) / e.cfg.bn;
+  const int64_t per_batch = causal_triangle(g.causal, e.cfg.bm, e.cfg.bn, tiles_m, tiles_n)
+                                ? tiles_m * (tiles_m + 1) / 2
+                                : tiles_m * tiles_n;
+  const double tiles = static_cast<double>(per_batch) * static_cast<double>(g.batch0) *
+                       static_cast<double>(g.batch1);
+  const double blocks = static_cast<double>((g.k + 63) / 64);
+  const double per_cu = std::ceil(tiles / cus);
+  if (index == 2) return 8.1 + per_cu * (5.8 * blocks + 3.2);
+  if (index == 9) return 5.0 + per_cu * (4.1 * blocks + 3.0);
+  if (g.causal == 2) {
+    const double part = 0.5 + 0.5 / static_cast<double>(tiles_m);
+    const double load = tiles > cus ? part * tiles / cus : 1.0;
+    return staged ? 2.8 + load * blocks * 4.0 : load * blocks * 7.2;
+  }
+  const double cut = g.k % 64 != 0 ? 2.0 : 0.0;  // the short last block runs by itself
+  return staged ? 2.7 + per_cu * (4.0 * blocks + 6.2 + cut) : 4.0 + per_cu * (8.2 * blocks + 3.6);
 }
 
 void gemm_mfma_tile(int index, int* bm, int* bn) {
@@ -1121,6 +1166,11 @@ hipError_t launch_gemm_mfma_grouped(const GroupArgs& ga, hipStream_t s) {
 }
 
 hipError_t launch_gemm_mfma(const GemmArgs& g, int index, hipStream_t s) {
+  if (index >= kMfmaCount) {
+    if (gemm_split_ok(g, index - kMfmaCount))
+      return launch_gemm_split(g, index - kMfmaCount, s);
+    index = 5;  // what the split kernels decline (other k blocks, no contraction)
+  }
   const MfmaEntry& e = kMfma[index];
   const int64_t tiles_m = (g.m + e.cfg.bm - 1) / e.cfg.bm;
   const int64_t tiles_n = (g.n + e.cfg.bn - 1) / e.cfg.bn;
@@ -1130,19 +1180,13 @@ hipError_t launch_gemm_mfma(const GemmArgs& g, int index, hipStream_t s) {
   const int64_t ntiles = per_batch * g.batch0 * g.batch1;
   const int64_t cap = int64_t(1) << 30;
   const unsigned grid = static_cast<unsigned>(ntiles < cap ? ntiles : cap);
-  // float4 loads need 16-byte aligned rows and batch origins
-  const int vec_ok = aligned16(g.A) && g.lda % 4 == 0 && g.sa0 % 4 == 0 && g.sa1 % 4 == 0 &&
-                     aligned16(g.B) && g.ldb % 4 == 0 && g.sb0 % 4 == 0 && g.sb1 % 4 == 0;
+  const int vec_ok = operands_aligned(g) ? 1 : 0;  // for the register-staged float4 loads
   auto kernel = e.kernel[g.ta * 2 + g.tb];
-  // the staged kernel takes whole slices only: K a multiple of its depth
-  // (and slice counts that fit in int)
-  const bool staged_ok = vec_ok && g.k % e.cfg.bk == 0 && g.k / e.cfg.bk <= INT32_MAX &&
-                         g.k_block / e.cfg.bk <= INT32_MAX && (!g.ta || g.m % 4 == 0) &&
-                         (g.tb || g.n % 4 == 0);
+  const bool staged_ok = gemm_mfma_staged_ok(g, index);
   unsigned blocks = grid;
   // the specialised stores where the product has a scale, a bias or a GELU array
   const int epi = (g.has_alpha || g.bias || g.G || g.gelu_in) ? 1 : 0;
-  if (e.staged[1][0] && staged_ok) kernel = e.staged[epi][g.ta * 2 + g.tb];
+  if (staged_ok) kernel = e.staged[epi][g.ta * 2 + g.tb];
   int cus = 0;
   if (gemm_mfma_ring_tiles(g, index, &cus) > cus) {
     kernel = e.ring[g.ta * 2 + g.tb];

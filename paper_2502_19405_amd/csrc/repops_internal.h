@@ -53,6 +53,22 @@ int64_t gemm_mfma_ring_tiles(const GemmArgs& g, int index, int* cus);
 void gemm_mfma_tile(int index, int* bm, int* bn);
 hipError_t launch_gemm_mfma_grouped(const GroupArgs& ga, hipStream_t s);
 
+// Compute units of the current device (0: not known).
+int device_cus();
+
+// Products whose k blocks are spread over the waves of a workgroup; the
+// matrix-core table continues with these entries (gemm_split_ok: whether entry
+// `index` takes this product).
+int gemm_split_count();
+const GemmConfig* gemm_split_config(int index);
+bool gemm_split_ok(const GemmArgs& g, int index);
+// Estimated time in us on a device of `cus` compute units, for the automatic
+// choice: of split entry `index`, and of matrix-core entry `index` (0, 2, 8, 9).
+double gemm_split_us(const GemmArgs& g, int index, int cus);
+double gemm_mfma_us(const GemmArgs& g, int index, int cus);
+int gemm_mfma_first_split();  // table index of split entry 0
+hipError_t launch_gemm_split(const GemmArgs& g, int index, hipStream_t s);
+
 hipError_t launch_gemm_simple(const GemmArgs& a, hipStream_t s);
 hipError_t launch_gemm_tiled(const GemmArgs& a, int index, hipStream_t s);
 hipError_t launch_gemm_mfma(const GemmArgs& a, int index, hipStream_t s);

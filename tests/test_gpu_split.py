@@ -1,0 +1,131 @@
+"""GPU parity, 0 ULP against the CPU oracle, of the matrix-core kernels that
+spread a product's k blocks over a workgroup's waves, of the staged kernels'
+short last block, and of the automatic choice between them and the other
+kernels.
+
+The contraction's length is taken around the ends of slices (16), blocks (64),
+rounds of blocks (4, 8, 16 or 32 blocks) and groups of blocks that share one
+instruction; rows and columns around the tiles' edges; operands in all four
+layouts, with leading dimensions and origins that are 16-byte aligned and that
+are not.
+"""
+import numpy as np
+import pytest
+
+import oracle
+from bitcmp import assert_bits_equal
+from gpu_util import announce, dev, host, same_bits
+from paper_2502_19405_amd import inputs
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def rp():
+    import torch
+    assert torch.cuda.is_available(), "GPU tests need a visible MI355X"
+    from paper_2502_19405_amd import repops
+    repops.load()
+    return repops
+
+
+def operand(a, transposed, pad):
+    """Device view of a, stored transposed or not, `pad` floats into each row."""
+    import torch
+    s = np.ascontiguousarray(a.T) if transposed else a
+    buf = torch.full((s.shape[0], s.shape[1] + pad), float("nan"), device="cuda:0")
+    v = buf[:, pad:] if pad else buf
+    v.copy_(dev(s))
+    return v.t() if transposed else v
+
+
+def entries(rp):
+    """Launches of the split kernels and of the staged entries with a short last
+    block (64-deep blocks of 16-deep slices, one ring turn each)."""
+    names = rp.gemm_configs(rp.LAUNCH_GEMM_MFMA)
+    out = [("auto", None)]
+    for i, n in enumerate(names):
+        if "/k" in n or i in (0, 8, 9):
+            out.append((n, rp.Launch(rp.LAUNCH_GEMM_MFMA, (i,))))
+    assert len(out) > 9
+    return out
+
+
+# (m, n): one row; tiles of 4, 16, 32 and 64 rows with one row or column more
+# or less than whole tiles; multiples of 4 for the staged kernels
+SHAPES = [(1, 68), (17, 31), (64, 132), (67, 65)]
+DEPTHS = [1, 3, 16, 18, 63, 64, 67, 100, 128, 191, 256, 260, 511, 1025, 2051]
+
+
+@pytest.mark.parametrize("k", DEPTHS)
+@pytest.mark.parametrize("pad", [0, 1, 4])
+def test_contraction_ends(rp, k, pad):
+    for m, n in SHAPES:
+        g = inputs.rng(40 * k + m + n)
+        A, B = inputs.normal(g, (m, k)), inputs.normal(g, (k, n))
+        bias = inputs.uniform(g, (n,), -0.1, 0.1)
+        want = oracle.matmul(A, B, bias)
+        dbias = dev(bias)
+        for ta in (0, 1):
+            for tb in (0, 1):
+                a, b = operand(A, ta, pad), operand(B, tb, pad)
+                for name, launch in entries(rp):
+                    announce("contraction end", m, n, k, pad, ta, tb, name)
+                    got = rp.matmul(a, b, dbias, launch=launch)
+                    assert_bits_equal(host(got), want, f"{m}x{n}x{k} pad {pad} {ta}{tb} {name}")
+
+
+@pytest.mark.parametrize("k", [64, 70, 333])
+def test_batched_causal_and_epilogues(rp, k):
+    """The same kernels with two batch strides, both causal masks, the GELU
+    output and the GELU backward's input."""
+    import torch
+    b0, b1, m, n = 2, 3, 70, 66
+    g = inputs.rng(8800 + k)
+    A, B = inputs.normal(g, (b0, b1, m, k)), inputs.normal(g, (b0, b1, n, k))
+    want = oracle.bmm(A, B, alpha=0.125, trans_b=True)
+    square = inputs.normal(g, (b0, b1, k, k))
+    square[..., np.triu(np.ones((k, k), bool), 1)] = 0.0
+    V = inputs.normal(g, (b0, b1, k, n))
+    want_v = oracle.bmm(square, V)
+    X = inputs.uniform(g, (m, n), -4.0, 4.0)
+    a2, b2 = A[0, 0], np.ascontiguousarray(B[0, 0].T)
+    prod = oracle.matmul(a2, b2)
+    want_g, want_gb = oracle.gelu(prod), oracle.gelu_backward(X, prod)
+    lower = np.tril(np.ones((m, n), bool))
+    for name, launch in entries(rp):
+        announce("batched, causal, epilogues", k, name)
+        for mask in (0, rp.CAUSAL_OUTPUT):
+            C = torch.full((b0, b1, m, n), float("nan"), device="cuda:0")
+            rp.bmm_raw(b0, b1, m, n, k, dev(A), b1 * m * k, m * k, k, 0, dev(B), b1 * n * k, n * k,
+                       k, 1, 0.125, C, b1 * m * n, m * n, n, launch=launch, causal=mask)
+            keep = lower if mask else np.ones((m, n), bool)
+            assert_bits_equal(np.where(keep, host(C), 0), np.where(keep, want, 0), f"{name} {mask}")
+        C = torch.full((b0, b1, k, n), float("nan"), device="cuda:0")
+        rp.bmm_raw(b0, b1, k, n, k, dev(square), b1 * k * k, k * k, k, 0, dev(V), b1 * k * n, k * n,
+                   n, 0, 1.0, C, b1 * k * n, k * n, n, launch=launch, causal=rp.CAUSAL_A)
+        assert_bits_equal(host(C), want_v, f"{name} causal A")
+        h, gl = rp.matmul_gelu(dev(a2), dev(b2), None, launch=launch)
+        assert_bits_equal(host(h), prod, f"{name} H")
+        assert_bits_equal(host(gl), want_g, f"{name} GELU")
+        gb = rp.matmul_gelu_backward(dev(a2), dev(b2), dev(X), launch=launch)
+        assert_bits_equal(host(gb), want_gb, f"{name} GELU backward")
+
+
+# tokens: few (each product by itself, on the split kernels) to many (one
+# grouped launch), with contractions over the tokens that end inside a slice
+@pytest.mark.parametrize("tokens", [1, 40, 333, 1001, 2050])
+def test_grouped_choice_keeps_the_bits(rp, tokens):
+    g = inputs.rng(6600 + tokens)
+    X, dY = inputs.normal(g, (tokens, 768)), inputs.normal(g, (tokens, 3072))
+    W = inputs.normal(g, (768, 3072))
+    dX_, dY_, W_ = dev(X), dev(dY), dev(W)
+    announce("grouped choice", tokens)
+    a, b = rp.matmul_grouped([(dY_, W_.t(), None, None), (dX_.t(), dY_, None, None)])
+    simple = rp.Launch(rp.LAUNCH_GEMM_SIMPLE)
+    assert same_bits(a, rp.matmul(dY_, W_.t(), launch=simple))
+    assert same_bits(b, rp.matmul(dX_.t(), dY_, launch=simple))
+    r, c = inputs.sample_indices(tokens, 256, tokens, 768)
+    assert_bits_equal(host(a)[r, c], oracle.matmul_at(dY, W, r, c, trans_b=True), "dX")
+    r, c = inputs.sample_indices(tokens + 1, 256, 768, 3072)
+    assert_bits_equal(host(b)[r, c], oracle.matmul_at(X, dY, r, c, trans_a=True), "dW")

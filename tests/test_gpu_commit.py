@@ -87,3 +87,41 @@ def test_commit_launch_edges(rp, leaves, short):
     data = inputs.rng(954 + leaves).integers(0, 256, leaves * 64 - short).astype(np.uint8)
     announce("commit launches", leaves, short)
     assert gpu_commit(rp, data, 64) == oracle.commit(data, 64)
+
+
+# tensors shorter than their chunk, alone or as the only leaf of a last workgroup
+# of 128 leaves (whole leaves before it), up to the largest chunk accepted
+@pytest.mark.parametrize("nbytes,chunk", [(1, 64), (100, 128), (100, 1 << 20), (4100, 1 << 20),
+                                          (100, 1 << 30), (128 * 4096 + 100, 4096),
+                                          (2 * 128 * 1024 + 1, 1024), (1 << 20, (1 << 20) + 64)])
+def test_commit_short_leaf_alone(rp, nbytes, chunk):
+    data = inputs.rng(955 + nbytes).integers(0, 256, nbytes).astype(np.uint8)
+    announce("commit short leaf", nbytes, chunk)
+    assert gpu_commit(rp, data, chunk) == oracle.commit(data, chunk)
+
+
+def test_commit_costs_its_bytes_not_its_chunk(rp):
+    """100 bytes take one leaf and no level whatever the chunk: the time with
+    1 MiB chunks is that with 128-byte ones.  (Walking the 16385 blocks of a 1 MiB
+    chunk with four barriers each takes over a hundred times as long; the factor 4
+    leaves room for the clock.)"""
+    import torch
+    t = dev(inputs.rng(956).integers(0, 256, 100).astype(np.uint8))
+
+    def us(chunk):
+        ws = torch.empty(64, dtype=torch.int32, device="cuda:0")
+        digest = torch.empty(32, dtype=torch.uint8, device="cuda:0")
+        best = float("inf")
+        for _ in range(5):
+            a, b = (torch.cuda.Event(enable_timing=True) for _ in range(2))
+            a.record()
+            for _ in range(20):
+                rp.commit(t, chunk, digest=digest, workspace=ws)
+            b.record()
+            b.synchronize()
+            best = min(best, a.elapsed_time(b) * 1e3 / 20)
+        return best
+
+    announce("commit short leaf time")
+    us(128)
+    assert us(1 << 20) < 4 * us(128)

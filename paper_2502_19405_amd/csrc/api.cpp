@@ -115,14 +115,14 @@ struct GemmChoice {
   double us;
 };
 
-GemmChoice choose_gemm(const GemmArgs& g) {
+// On a device of `cus` compute units (0: not known); host arithmetic only.
+GemmChoice choose_gemm(const GemmArgs& g, int cus) {
   // Matrix cores for the fused order (their single-term updates are the fma
   // chain): with 64-deep k blocks, the entry with the smallest estimated time
   // among the large tile that suits the product and the kernels that spread the
   // k blocks over a workgroup's waves; vector tiles for the unfused order; the
   // simple path for block lengths no tile divides.
   const int64_t outputs = g.m * g.n * g.batch0 * g.batch1;
-  const int cus = g.fused ? repops::device_cus() : 0;
   uint32_t pref = 0;  // 128 x 128 tiles, 8 waves, ring
   double us = 0.0;
   if (cus > 0 && repops::gemm_split_ok(g, 0)) {
@@ -138,8 +138,7 @@ GemmChoice choose_gemm(const GemmArgs& g) {
       // the large tile: staged, register-staged, or (short k) the persistent ring
       take(0, repops::gemm_mfma_us(g, 0, cus));
       take(2, repops::gemm_mfma_us(g, 2, cus));
-      int ring_cus = 0;
-      if (g.k <= 256 && repops::gemm_mfma_ring_tiles(g, 9, &ring_cus) > 0)
+      if (g.k <= 256 && repops::gemm_mfma_ring_tiles(g, 9) > 0)
         take(9, repops::gemm_mfma_us(g, 9, cus));
     }
     const uint32_t first = static_cast<uint32_t>(repops::gemm_mfma_first_split());
@@ -194,6 +193,67 @@ double grouped_us(const repops::GroupArgs& ga, int cus) {
   return 2.7 + spans[count - 1].free;
 }
 
+GemmArgs group_args(const repops_order_t* order, const repops_gemm_desc_t& d) {
+  GemmArgs g{};
+  g.batch0 = 1; g.batch1 = 1; g.m = d.m; g.n = d.n; g.k = d.k;
+  g.A = d.A; g.lda = d.lda; g.ta = d.trans_a;
+  g.B = d.B; g.ldb = d.ldb; g.tb = d.trans_b;
+  g.C = d.C; g.ldc = d.ldc;
+  g.bias = d.bias; g.alpha = 1.0f; g.has_alpha = 0;
+  g.gelu_in = d.gelu_in; g.ld_gelu_in = d.ld_gelu_in;
+  g.k_block = order->k_block;
+  g.fused = order->k_inner == REPOPS_K_FMA ? 1 : 0;
+  return g;
+}
+
+// How the products of a grouped call run on a device of `cus` compute units: one
+// launch of entry 0's tile (*one, and *ga describes it) or one after another.
+// Host arithmetic only.
+repops_status_t plan_group(const repops_order_t* order, int count, const GemmArgs* g, int cus,
+                           repops::GroupArgs* ga, bool* one) {
+  *one = order->k_inner == REPOPS_K_FMA && (order->k_block == 0 || order->k_block % 16 == 0);
+  int idx[REPOPS_MAX_GROUP], n = 0;
+  for (int p = 0; p < count; ++p) {
+    if (g[p].m == 0 || g[p].n == 0) continue;
+    idx[n++] = p;
+    *one = *one && g[p].k > 0 && repops::gemm_mfma_staged_ok(g[p], 0);
+  }
+  if (!*one) return REPOPS_OK;
+  // One launch: the products with the longest contraction first, so that
+  // their tiles start first and the short ones fill the compute units behind
+  // them.
+  for (int a = 1; a < n; ++a)
+    for (int b = a; b > 0 && g[idx[b]].k > g[idx[b - 1]].k; --b) {
+      const int t = idx[b]; idx[b] = idx[b - 1]; idx[b - 1] = t;
+    }
+  int bm, bn, threads;
+  repops::gemm_mfma_tile(0, &bm, &bn, &threads);
+  *ga = repops::GroupArgs{};
+  ga->count = n;
+  ga->first[0] = 0;
+  for (int i = 0; i < n; ++i) {
+    ga->g[i] = g[idx[i]];
+    ga->tiles_m[i] = (ga->g[i].m + bm - 1) / bm;
+    ga->tiles_n[i] = (ga->g[i].n + bn - 1) / bn;
+    ga->first[i + 1] = ga->first[i] + ga->tiles_m[i] * ga->tiles_n[i];
+  }
+  if (ga->first[n] > kMaxDim) return REPOPS_ERR_SHAPE;
+  if (ga->first[n] > repops::max_workgroups(threads)) {  // one workgroup per tile
+    *one = false;
+    return REPOPS_OK;
+  }
+  // One by one where the products' own launches are estimated faster by more
+  // than the estimates' scatter: few tokens, whose tiles leave most units idle.
+  double alone = 0.0;
+  for (int i = 0; i < n && cus > 0; ++i) {
+    const double us = choose_gemm(ga->g[i], cus).us;
+    if (us <= 0.0) alone = INFINITY;  // not estimated
+    alone += us;
+  }
+  if (cus > 0 && alone < 0.88 * grouped_us(*ga, cus)) *one = false;
+  return REPOPS_OK;
+}
+
 repops_status_t run_gemm(const repops_order_t* order, GemmArgs& g, const repops_launch_t* launch,
                          hipStream_t stream) {
   if (!order_valid(order)) return REPOPS_ERR_ORDER;
@@ -213,7 +273,7 @@ repops_status_t run_gemm(const repops_order_t* order, GemmArgs& g, const repops_
     }
   }
   if (kind == REPOPS_LAUNCH_AUTO) {
-    const GemmChoice c = choose_gemm(g);
+    const GemmChoice c = choose_gemm(g, g.fused ? repops::device_cus() : 0);
     kind = c.kind;
     index = c.index;
   }
@@ -559,16 +619,7 @@ repops_status_t repops_matmul_grouped(const repops_order_t* order, int32_t count
   GemmArgs g[REPOPS_MAX_GROUP];
   bool live[REPOPS_MAX_GROUP];
   for (int p = 0; p < count; ++p) {
-    const repops_gemm_desc_t& d = descs[p];
-    g[p] = GemmArgs{};
-    g[p].batch0 = 1; g[p].batch1 = 1; g[p].m = d.m; g[p].n = d.n; g[p].k = d.k;
-    g[p].A = d.A; g[p].lda = d.lda; g[p].ta = d.trans_a;
-    g[p].B = d.B; g[p].ldb = d.ldb; g[p].tb = d.trans_b;
-    g[p].C = d.C; g[p].ldc = d.ldc;
-    g[p].bias = d.bias; g[p].alpha = 1.0f; g[p].has_alpha = 0;
-    g[p].gelu_in = d.gelu_in; g[p].ld_gelu_in = d.ld_gelu_in;
-    g[p].k_block = order->k_block;
-    g[p].fused = order->k_inner == REPOPS_K_FMA ? 1 : 0;
+    g[p] = group_args(order, descs[p]);
     repops_status_t st = check_operands(g[p]);
     if (st == REPOPS_OK) st = check_gelu_in(g[p]);
     if (st != REPOPS_OK) return st;
@@ -598,55 +649,22 @@ repops_status_t repops_matmul_grouped(const repops_order_t* order, int32_t count
     }
   }
   hipStream_t s = static_cast<hipStream_t>(hip_stream);
-  bool one = order->k_inner == REPOPS_K_FMA && (order->k_block == 0 || order->k_block % 16 == 0);
-  int n_live = 0;
-  for (int p = 0; p < count; ++p) {
-    if (!live[p]) continue;
-    ++n_live;
-    one = one && g[p].k > 0 && repops::gemm_mfma_staged_ok(g[p], 0);
-  }
-  if (n_live == 0) return REPOPS_OK;
-  auto one_by_one = [&]() -> repops_status_t {
+  bool any = false;
+  for (int p = 0; p < count; ++p) any = any || live[p];
+  if (!any) return REPOPS_OK;
+  repops::GroupArgs ga;
+  bool one;
+  const int cus = order->k_inner == REPOPS_K_FMA ? repops::device_cus() : 0;
+  const repops_status_t planned = plan_group(order, count, g, cus, &ga, &one);
+  if (planned != REPOPS_OK) return planned;
+  if (!one) {
     for (int p = 0; p < count; ++p) {
       if (!live[p]) continue;
       const repops_status_t st = run_gemm(order, g[p], nullptr, s);
       if (st != REPOPS_OK) return st;
     }
     return REPOPS_OK;
-  };
-  if (!one) return one_by_one();
-  // One launch: the products with the longest contraction first, so that
-  // their tiles start first and the short ones fill the compute units behind
-  // them.
-  int idx[REPOPS_MAX_GROUP], n = 0;
-  for (int p = 0; p < count; ++p)
-    if (live[p]) idx[n++] = p;
-  for (int a = 1; a < n; ++a)
-    for (int b = a; b > 0 && g[idx[b]].k > g[idx[b - 1]].k; --b) {
-      const int t = idx[b]; idx[b] = idx[b - 1]; idx[b - 1] = t;
-    }
-  int bm, bn;
-  repops::gemm_mfma_tile(0, &bm, &bn);
-  repops::GroupArgs ga{};
-  ga.count = n;
-  ga.first[0] = 0;
-  for (int i = 0; i < n; ++i) {
-    ga.g[i] = g[idx[i]];
-    ga.tiles_m[i] = (ga.g[i].m + bm - 1) / bm;
-    ga.tiles_n[i] = (ga.g[i].n + bn - 1) / bn;
-    ga.first[i + 1] = ga.first[i] + ga.tiles_m[i] * ga.tiles_n[i];
   }
-  if (ga.first[n] > kMaxDim) return REPOPS_ERR_SHAPE;
-  // One by one where the products' own launches are estimated faster by more
-  // than the estimates' scatter: few tokens, whose tiles leave most units idle.
-  const int cus = repops::device_cus();
-  double alone = 0.0;
-  for (int i = 0; i < n && cus > 0; ++i) {
-    const double us = choose_gemm(ga.g[i]).us;
-    if (us <= 0.0) alone = INFINITY;  // not estimated
-    alone += us;
-  }
-  if (cus > 0 && alone < 0.88 * grouped_us(ga, cus)) return one_by_one();
   return hip_status(repops::launch_gemm_mfma_grouped(ga, s));
 }
 
@@ -1291,6 +1309,40 @@ repops_status_t repops_gelu_erf_backward(const repops_order_t* order, int64_t n,
   if (st != REPOPS_OK || n == 0) return st;
   return hip_status(repops::launch_gelu_bwd(n, X, dY, dX, threads, max_blocks,
                                             static_cast<hipStream_t>(hip_stream), true));
+}
+
+// ---------------------------------------------------------------------------
+// The launch rules on a device of `cus` compute units, for the tests (no part of
+// the public interface; host arithmetic only, the operands are not read)
+// ---------------------------------------------------------------------------
+
+// repops_bmm_causal's arguments (causal 0: repops_bmm's, one batch dimension);
+// receives the kind and table index REPOPS_LAUNCH_AUTO takes.
+void repops_internal_gemm_choice(const repops_order_t* order, int64_t batch, int64_t m, int64_t n,
+                                 int64_t k, int64_t lda, int32_t trans_a, int64_t ldb,
+                                 int32_t trans_b, int32_t causal, int32_t cus, uint32_t* kind,
+                                 uint32_t* index) {
+  GemmArgs g{};
+  g.batch0 = batch; g.batch1 = 1; g.m = m; g.n = n; g.k = k;
+  g.lda = lda; g.ta = trans_a;
+  g.ldb = ldb; g.tb = trans_b;
+  g.k_block = order->k_block;
+  g.fused = order->k_inner == REPOPS_K_FMA ? 1 : 0;
+  g.causal = causal;
+  const GemmChoice c = choose_gemm(g, g.fused ? cus : 0);
+  *kind = c.kind;
+  *index = c.index;
+}
+
+// 1 where repops_matmul_grouped runs these products in one launch.
+int32_t repops_internal_grouped_choice(const repops_order_t* order, int32_t count,
+                                       const repops_gemm_desc_t* descs, int32_t cus) {
+  GemmArgs g[REPOPS_MAX_GROUP];
+  for (int p = 0; p < count; ++p) g[p] = group_args(order, descs[p]);
+  repops::GroupArgs ga;
+  bool one;
+  const int known = order->k_inner == REPOPS_K_FMA ? cus : 0;
+  return plan_group(order, count, g, known, &ga, &one) == REPOPS_OK && one ? 1 : 0;
 }
 
 }  // extern "C"

@@ -218,10 +218,10 @@ const TiledEntry kTiled[] = {
 };
 constexpr int kTiledCount = sizeof(kTiled) / sizeof(kTiled[0]);
 
-int64_t grid_for(int64_t ntiles) {
-  // Enough workgroups to cover every tile once, capped at what the hardware
-  // grid allows; the kernels loop over the rest.
-  const int64_t cap = int64_t(1) << 30;
+int64_t grid_for(int64_t ntiles, int threads) {
+  // Enough workgroups to cover every tile once, capped at what one launch may
+  // have; the kernels loop over the rest.
+  const int64_t cap = max_workgroups(threads);
   return ntiles < cap ? ntiles : cap;
 }
 
@@ -235,7 +235,7 @@ const GemmConfig* gemm_tiled_config(int index) {
 hipError_t launch_gemm_simple(const GemmArgs& g, hipStream_t s) {
   const int64_t tiles_m = (g.m + 15) / 16, tiles_n = (g.n + 15) / 16;
   const int64_t ntiles = tiles_m * tiles_n * g.batch0 * g.batch1;
-  const dim3 grid(static_cast<unsigned>(grid_for(ntiles)));
+  const dim3 grid(static_cast<unsigned>(grid_for(ntiles, 256)));
   if (g.fused)
     hipLaunchKernelGGL(gemm_simple_kernel<true>, grid, dim3(256), 0, s, g, tiles_m, tiles_n, ntiles);
   else
@@ -248,7 +248,7 @@ hipError_t launch_gemm_tiled(const GemmArgs& g, int index, hipStream_t s) {
   const int64_t tiles_m = (g.m + e.cfg.bm - 1) / e.cfg.bm;
   const int64_t tiles_n = (g.n + e.cfg.bn - 1) / e.cfg.bn;
   const int64_t ntiles = tiles_m * tiles_n * g.batch0 * g.batch1;
-  const dim3 grid(static_cast<unsigned>(grid_for(ntiles)));
+  const dim3 grid(static_cast<unsigned>(grid_for(ntiles, e.threads)));
   hipLaunchKernelGGL(g.fused ? e.fused : e.unfused, grid, dim3(e.threads), 0, s, g, tiles_m,
                      tiles_n, ntiles);
   return hipGetLastError();

@@ -1104,11 +1104,10 @@ int device_cus() {
 // Tiles of a launch that the ring form of entry `index` can take, else 0: every
 // tile makes whole ring turns of one 64-deep k block each (16-deep slices,
 // four slots) over the same K, the staged kernel's layout rules hold, and no
-// tile is skipped or cut short.  *cus receives the device's compute units; the
-// launch takes the ring form when the tiles outnumber them.
-int64_t gemm_mfma_ring_tiles(const GemmArgs& g, int index, int* cus) {
+// tile is skipped or cut short.  The launch takes the ring form when the tiles
+// outnumber the device's compute units.
+int64_t gemm_mfma_ring_tiles(const GemmArgs& g, int index) {
   const MfmaEntry& e = kMfma[index];
-  *cus = 0;
   if (!e.ring[0] || e.cfg.bk != 16 || g.k <= 0 || g.k_block != 64 || g.k % 64 != 0 ||
       !gemm_mfma_staged_ok(g, index))
     return 0;
@@ -1116,8 +1115,6 @@ int64_t gemm_mfma_ring_tiles(const GemmArgs& g, int index, int* cus) {
   const int64_t tiles_n = (g.n + e.cfg.bn - 1) / e.cfg.bn;
   const bool tri = causal_triangle(g.causal, e.cfg.bm, e.cfg.bn, tiles_m, tiles_n);
   if (g.causal != 0 && !tri) return 0;
-  *cus = device_cus();
-  if (*cus == 0) return 0;
   const int64_t per_batch = tri ? tiles_m * (tiles_m + 1) / 2 : tiles_m * tiles_n;
   return per_batch * g.batch0 * g.batch1;
 }
@@ -1152,9 +1149,10 @@ double gemm_mfma_us(const GemmArgs& g, int index, int cus) {
   return staged ? 2.7 + per_cu * (4.0 * blocks + 6.2 + cut) : 4.0 + per_cu * (8.2 * blocks + 3.6);
 }
 
-void gemm_mfma_tile(int index, int* bm, int* bn) {
+void gemm_mfma_tile(int index, int* bm, int* bn, int* threads) {
   *bm = kMfma[index].cfg.bm;
   *bn = kMfma[index].cfg.bn;
+  *threads = kMfma[index].threads;
 }
 
 hipError_t launch_gemm_mfma_grouped(const GroupArgs& ga, hipStream_t s) {
@@ -1178,7 +1176,7 @@ hipError_t launch_gemm_mfma(const GemmArgs& g, int index, hipStream_t s) {
                                 ? tiles_m * (tiles_m + 1) / 2
                                 : tiles_m * tiles_n;
   const int64_t ntiles = per_batch * g.batch0 * g.batch1;
-  const int64_t cap = int64_t(1) << 30;
+  const int64_t cap = max_workgroups(e.threads);
   const unsigned grid = static_cast<unsigned>(ntiles < cap ? ntiles : cap);
   const int vec_ok = operands_aligned(g) ? 1 : 0;  // for the register-staged float4 loads
   auto kernel = e.kernel[g.ta * 2 + g.tb];
@@ -1187,8 +1185,9 @@ hipError_t launch_gemm_mfma(const GemmArgs& g, int index, hipStream_t s) {
   // the specialised stores where the product has a scale, a bias or a GELU array
   const int epi = (g.has_alpha || g.bias || g.G || g.gelu_in) ? 1 : 0;
   if (staged_ok) kernel = e.staged[epi][g.ta * 2 + g.tb];
-  int cus = 0;
-  if (gemm_mfma_ring_tiles(g, index, &cus) > cus) {
+  const int64_t ring = gemm_mfma_ring_tiles(g, index);
+  const int cus = ring > 0 ? device_cus() : 0;
+  if (cus > 0 && ring > cus) {
     kernel = e.ring[g.ta * 2 + g.tb];
     blocks = static_cast<unsigned>(cus);
   }

@@ -569,10 +569,11 @@ bool gemm_split_ok(const GemmArgs& g, int index) {
   const SplitEntry& e = kSplit[index];
   const int64_t tiles_m = (g.m + e.cfg.bm - 1) / e.cfg.bm, tiles_n = (g.n + e.cfg.bn - 1) / e.cfg.bn;
   constexpr int64_t kLd = int64_t(1) << 22;  // lane offsets stay within 32 bits
+  // one workgroup per tile; the tile arithmetic is 32-bit (4 tile rows at a time)
+  const int64_t cap = max_workgroups(64 * e.ks);
   return g.fused && g.k_block == kBlock && g.k > 0 && g.k <= INT32_MAX / 2 && g.lda <= kLd && g.ldb <= kLd &&
-         tiles_m <= INT32_MAX && tiles_n <= INT32_MAX / 8 &&
-         g.batch0 * g.batch1 <= INT32_MAX &&
-         static_cast<unsigned __int128>(tiles_m) * tiles_n * (g.batch0 * g.batch1) <= INT32_MAX;
+         g.batch0 * g.batch1 <= cap &&
+         static_cast<unsigned __int128>(tiles_m) * tiles_n * (g.batch0 * g.batch1) <= static_cast<uint64_t>(cap);
 }
 
 double gemm_split_us(const GemmArgs& g, int index, int cus) {

@@ -23,6 +23,11 @@ struct GemmArgs {
                       // zero at kk > i (their kernels skip the all-zero k blocks)
 };
 
+// HIP refuses a launch of 2^32 threads or more.  Workgroups of `threads` threads
+// that a launch may have; kernels that loop over their tiles take the rest in
+// further turns, the others are not offered.
+constexpr int64_t max_workgroups(int threads) { return int64_t(UINT32_MAX) / threads; }
+
 struct GemmConfig {
   const char* name;
   int bm, bn, bk;
@@ -46,11 +51,12 @@ struct GroupArgs {
 };
 bool gemm_mfma_staged_ok(const GemmArgs& g, int index);
 // Tiles the persistent ring form of matrix-core entry `index` would take for
-// this product (0 when it cannot); *cus receives the device's compute units,
-// and the launch takes the ring form when the tiles outnumber them.
-int64_t gemm_mfma_ring_tiles(const GemmArgs& g, int index, int* cus);
-// Tile edge lengths of table entry `index` (for the grouped launch's tiles).
-void gemm_mfma_tile(int index, int* bm, int* bn);
+// this product (0 when it cannot); the launch takes the ring form when they
+// outnumber the device's compute units.
+int64_t gemm_mfma_ring_tiles(const GemmArgs& g, int index);
+// Tile edge lengths and workgroup size of table entry `index` (for the grouped
+// launch's tiles).
+void gemm_mfma_tile(int index, int* bm, int* bn, int* threads);
 hipError_t launch_gemm_mfma_grouped(const GroupArgs& ga, hipStream_t s);
 
 // Compute units of the current device (0: not known).

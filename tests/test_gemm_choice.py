@@ -1,0 +1,55 @@
+"""The automatic choice of a product's launch, on the CPU: the rule is host
+arithmetic on sizes, strides and the number of compute units, so its routes can
+be checked without a device (the bits of every route are the GPU tests')."""
+import ctypes
+import os
+import re
+
+import pytest
+
+LIB = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))),
+                   "paper_2502_19405_amd", "librepops.so")
+CUS = 256  # compute units of an MI355X
+
+
+@pytest.fixture(scope="module")
+def rp():
+    if not os.path.exists(LIB):
+        pytest.fail("librepops.so is not built (run python -m paper_2502_19405_amd.build)")
+    from paper_2502_19405_amd import repops
+    repops.load()
+    return repops
+
+
+def choice(rp, m, n, k, batch=1, lda=None, ta=0, ldb=None, tb=0, causal=0, k_block=64, cus=CUS):
+    """(kind, index) of REPOPS_LAUNCH_AUTO; dense leading dimensions by default."""
+    i64, i32, u32 = ctypes.c_int64, ctypes.c_int32, ctypes.c_uint32
+    kind, index = u32(), u32()
+    rp.load().repops_internal_gemm_choice(
+        ctypes.byref(rp.Order(k_block=k_block).c()), i64(batch), i64(m), i64(n), i64(k),
+        i64(lda or (m if ta else k)), i32(ta), i64(ldb or (k if tb else n)), i32(tb), i32(causal),
+        i32(cus), ctypes.byref(kind), ctypes.byref(index))
+    return kind.value, index.value
+
+
+def tile(rp, index):
+    """Rows, columns and, of a split entry, waves of a matrix-core table entry."""
+    name = rp.gemm_configs(rp.LAUNCH_GEMM_MFMA)[index]
+    bm, bn = (int(x) for x in name.split("x")[:2])
+    waves = re.search(r"/k(\d+)", name)
+    return bm, bn, int(waves.group(1)) if waves else None
+
+
+@pytest.mark.parametrize("m,n,k,batch", [(1, 1, 64, 1 << 24), (1, 1, 256, 1 << 25),
+                                         (1 << 30, 4, 4, 1), (1, 1 << 28, 4, 1),
+                                         (4, 4, 64, 10_000_000), (16, 16, 128, (1 << 23) + 1),
+                                         (16, 16, 128, 1 << 22)])
+@pytest.mark.parametrize("ta", [0, 1])
+@pytest.mark.parametrize("tb", [0, 1])
+def test_a_split_launch_stays_below_2_to_the_32_threads(rp, m, n, k, batch, ta, tb):
+    """One workgroup per tile, and HIP refuses launches of 2^32 threads or more."""
+    kind, index = choice(rp, m, n, k, batch, ta=ta, tb=tb)
+    assert kind == rp.LAUNCH_GEMM_MFMA
+    bm, bn, waves = tile(rp, index)
+    if waves:
+        assert -(-m // bm) * -(-n // bn) * batch * 64 * waves < 1 << 32

@@ -129,3 +129,26 @@ def test_grouped_choice_keeps_the_bits(rp, tokens):
     assert_bits_equal(host(a)[r, c], oracle.matmul_at(dY, W, r, c, trans_b=True), "dX")
     r, c = inputs.sample_indices(tokens + 1, 256, 768, 3072)
     assert_bits_equal(host(b)[r, c], oracle.matmul_at(X, dY, r, c, trans_a=True), "dW")
+
+
+def test_products_of_more_tiles_than_one_launch_holds(rp):
+    """2^24 products of one output each: a workgroup per tile would be 2^32 threads
+    or more, so the split kernels decline and the others loop over the rest.  All
+    batch elements read the same operands, so every output is the one oracle value."""
+    import torch
+    k, batch = 64, 1 << 24
+    g = inputs.rng(8900)
+    A, B = inputs.normal(g, (1, k)), inputs.normal(g, (1, k))
+    want = oracle.matmul(A, np.ascontiguousarray(B.T))
+    split = next(i for i, n in enumerate(rp.gemm_configs(rp.LAUNCH_GEMM_MFMA)) if "/k" in n)
+    dA, dB = dev(A), dev(B)
+    C = torch.empty(batch, device="cuda:0")
+    for name, launch in [("auto", None), ("simple", rp.Launch(rp.LAUNCH_GEMM_SIMPLE)),
+                         ("mfma0", rp.Launch(rp.LAUNCH_GEMM_MFMA, (0,))),
+                         ("split", rp.Launch(rp.LAUNCH_GEMM_MFMA, (split,)))]:
+        announce("more tiles than one launch holds", name)
+        C.fill_(float("nan"))
+        rp.bmm_raw(batch, 1, 1, 1, k, dA, 0, 0, k, 0, dB, 0, 0, k, 1, 1.0, C, 1, 1, 1,
+                   launch=launch)
+        assert_bits_equal(host(C[:1]), want.reshape(1), name)
+        assert same_bits(C, C[:1].expand(batch)), name

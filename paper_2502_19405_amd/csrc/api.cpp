@@ -118,20 +118,24 @@ struct GemmChoice {
 // On a device of `cus` compute units (0: not known); host arithmetic only.
 GemmChoice choose_gemm(const GemmArgs& g, int cus) {
   // Matrix cores for the fused order (their single-term updates are the fma
-  // chain): with 64-deep k blocks, the entry with the smallest estimated time
-  // among the large tile that suits the product and the kernels that spread the
-  // k blocks over a workgroup's waves; vector tiles for the unfused order; the
+  // chain): where a split kernel takes the product (64-deep k blocks), the entry
+  // with the smallest estimated time among them and the large tile that suits the
+  // product; else by the number of outputs and the depth; vector tiles for the unfused order; the
   // simple path for block lengths no tile divides.
   const int64_t outputs = g.m * g.n * g.batch0 * g.batch1;
   uint32_t pref = 0;  // 128 x 128 tiles, 8 waves, ring
   double us = 0.0;
-  if (cus > 0 && repops::gemm_split_ok(g, 0)) {
-    auto take = [&](uint32_t index, double t) {
-      if (us <= 0.0 || t < us) {
-        us = t;
-        pref = index;
-      }
-    };
+  auto take = [&](uint32_t index, double t) {
+    if (us <= 0.0 || t < us) {
+      us = t;
+      pref = index;
+    }
+  };
+  const uint32_t first = static_cast<uint32_t>(repops::gemm_mfma_first_split());
+  for (int i = 0; i < repops::gemm_split_count() && cus > 0; ++i)
+    if (repops::gemm_split_ok(g, i))
+      take(first + static_cast<uint32_t>(i), repops::gemm_split_us(g, i, cus));
+  if (us > 0.0) {
     if (g.causal == 2) {
       take(8, repops::gemm_mfma_us(g, 8, cus));  // 64-row tiles
     } else {
@@ -141,13 +145,14 @@ GemmChoice choose_gemm(const GemmArgs& g, int cus) {
       if (g.k <= 256 && repops::gemm_mfma_ring_tiles(g, 9) > 0)
         take(9, repops::gemm_mfma_us(g, 9, cus));
     }
-    const uint32_t first = static_cast<uint32_t>(repops::gemm_mfma_first_split());
-    for (int i = 0; i < repops::gemm_split_count(); ++i)
-      if (repops::gemm_split_ok(g, i)) take(first + static_cast<uint32_t>(i), repops::gemm_split_us(g, i, cus));
   } else if (outputs <= (int64_t(1) << 20)) {
     pref = 5;  // small outputs: 64 x 64 tiles
   } else if (g.k <= 256) {
-    pref = 2;  // short k: register-staged slices
+    // short k: the persistent ring form where each compute unit takes at least
+    // four tiles in turn (products the split kernels decline for a leading
+    // dimension over 2^22 or for their number of tiles), else register-staged
+    // slices
+    pref = cus > 0 && repops::gemm_mfma_ring_tiles(g, 9) >= 4 * static_cast<int64_t>(cus) ? 9 : 2;
   } else if (g.causal == 2) {
     pref = 8;
   }

@@ -53,3 +53,18 @@ def test_a_split_launch_stays_below_2_to_the_32_threads(rp, m, n, k, batch, ta, 
     bm, bn, waves = tile(rp, index)
     if waves:
         assert -(-m // bm) * -(-n // bn) * batch * 64 * waves < 1 << 32
+
+
+@pytest.mark.parametrize("m,n,k,ld", [(4096, 4096, 64, {"lda": (1 << 22) + 4}),
+                                      (4096, 4096, 256, {"ldb": (1 << 22) + 4}),
+                                      (128, 1 << 23, 64, {}),          # B's rows
+                                      (1 << 23, 128, 128, {"ta": 1}),  # A's columns
+                                      (1, 1, 64, {"batch": 1 << 24, "tb": 1})])
+def test_short_contractions_the_split_kernels_decline_keep_the_ring_form(rp, m, n, k, ld):
+    """Leading dimensions over 2^22, or too many tiles for one workgroup each: with
+    at least four tiles of 128 x 128 per compute unit the ring form runs them
+    (128 x 8388608 outputs at k 64: 1910 us against 2430 on entry 2)."""
+    assert choice(rp, m, n, k, **ld) == (rp.LAUNCH_GEMM_MFMA, 9)
+    if "batch" not in ld:  # few tiles: the register-staged form, as for other short k
+        few = {"lda": 1 << 23, "ldb": 1 << 23}
+        assert choice(rp, 2048, 2048, k, **few) == (rp.LAUNCH_GEMM_MFMA, 2)

@@ -115,6 +115,22 @@ struct GemmChoice {
   double us;
 };
 
+// Estimated time in us of matrix-core entry `index` on `cus` compute units; 0
+// where the automatic choice does not offer it: the split kernels for what they
+// take, 64-row tiles for products whose A is zero above its diagonal, for the
+// others the large tile, staged, register-staged or (short k) in its persistent
+// ring form.
+double estimated_us(const GemmArgs& g, uint32_t index, int cus) {
+  const int split = static_cast<int>(index) - repops::gemm_mfma_first_split();
+  if (split >= 0)
+    return repops::gemm_split_ok(g, split) ? repops::gemm_split_us(g, split, cus) : 0.0;
+  const bool offered =
+      g.causal == 2 ? index == 8
+                    : index == 0 || index == 2 ||
+                          (index == 9 && g.k <= 256 && repops::gemm_mfma_ring_tiles(g, 9) > 0);
+  return offered ? repops::gemm_mfma_us(g, static_cast<int>(index), cus) : 0.0;
+}
+
 // On a device of `cus` compute units (0: not known); host arithmetic only.
 GemmChoice choose_gemm(const GemmArgs& g, int cus) {
   // Matrix cores for the fused order (their single-term updates are the fma
@@ -125,26 +141,17 @@ GemmChoice choose_gemm(const GemmArgs& g, int cus) {
   const int64_t outputs = g.m * g.n * g.batch0 * g.batch1;
   uint32_t pref = 0;  // 128 x 128 tiles, 8 waves, ring
   double us = 0.0;
-  auto take = [&](uint32_t index, double t) {
-    if (us <= 0.0 || t < us) {
+  auto take = [&](uint32_t index) {
+    const double t = estimated_us(g, index, cus);
+    if (t > 0.0 && (us <= 0.0 || t < us)) {
       us = t;
       pref = index;
     }
   };
-  const uint32_t first = static_cast<uint32_t>(repops::gemm_mfma_first_split());
   for (int i = 0; i < repops::gemm_split_count() && cus > 0; ++i)
-    if (repops::gemm_split_ok(g, i))
-      take(first + static_cast<uint32_t>(i), repops::gemm_split_us(g, i, cus));
+    take(static_cast<uint32_t>(repops::gemm_mfma_first_split() + i));
   if (us > 0.0) {
-    if (g.causal == 2) {
-      take(8, repops::gemm_mfma_us(g, 8, cus));  // 64-row tiles
-    } else {
-      // the large tile: staged, register-staged, or (short k) the persistent ring
-      take(0, repops::gemm_mfma_us(g, 0, cus));
-      take(2, repops::gemm_mfma_us(g, 2, cus));
-      if (g.k <= 256 && repops::gemm_mfma_ring_tiles(g, 9) > 0)
-        take(9, repops::gemm_mfma_us(g, 9, cus));
-    }
+    for (uint32_t i : {0u, 2u, 8u, 9u}) take(i);
   } else if (outputs <= (int64_t(1) << 20)) {
     pref = 5;  // small outputs: 64 x 64 tiles
   } else if (g.k <= 256) {
@@ -1321,22 +1328,38 @@ repops_status_t repops_gelu_erf_backward(const repops_order_t* order, int64_t n,
 // the public interface; host arithmetic only, the operands are not read)
 // ---------------------------------------------------------------------------
 
-// repops_bmm_causal's arguments (causal 0: repops_bmm's, one batch dimension);
-// receives the kind and table index REPOPS_LAUNCH_AUTO takes.
+static GemmArgs shape_args(const repops_order_t* order, int64_t batch, int64_t m, int64_t n,
+                           int64_t k, int64_t lda, int32_t trans_a, int64_t ldb, int32_t trans_b,
+                           int32_t causal) {
+  GemmArgs g{};
+  g.batch0 = batch; g.batch1 = 1; g.m = m; g.n = n; g.k = k;
+  g.lda = lda; g.ta = trans_a; g.sa0 = batch == 1 ? 0 : (trans_a ? k : m) * lda;
+  g.ldb = ldb; g.tb = trans_b; g.sb0 = batch == 1 ? 0 : (trans_b ? n : k) * ldb;
+  g.k_block = order->k_block;
+  g.fused = order->k_inner == REPOPS_K_FMA ? 1 : 0;
+  g.causal = causal;
+  return g;
+}
+
+// Of a batch of dense products (causal: repops_bmm_causal's mask or 0): the kind
+// and table index REPOPS_LAUNCH_AUTO takes.
 void repops_internal_gemm_choice(const repops_order_t* order, int64_t batch, int64_t m, int64_t n,
                                  int64_t k, int64_t lda, int32_t trans_a, int64_t ldb,
                                  int32_t trans_b, int32_t causal, int32_t cus, uint32_t* kind,
                                  uint32_t* index) {
-  GemmArgs g{};
-  g.batch0 = batch; g.batch1 = 1; g.m = m; g.n = n; g.k = k;
-  g.lda = lda; g.ta = trans_a;
-  g.ldb = ldb; g.tb = trans_b;
-  g.k_block = order->k_block;
-  g.fused = order->k_inner == REPOPS_K_FMA ? 1 : 0;
-  g.causal = causal;
+  const GemmArgs g = shape_args(order, batch, m, n, k, lda, trans_a, ldb, trans_b, causal);
   const GemmChoice c = choose_gemm(g, g.fused ? cus : 0);
   *kind = c.kind;
   *index = c.index;
+}
+
+// The estimate for one matrix-core entry (0: not offered).
+double repops_internal_gemm_estimate(const repops_order_t* order, int64_t batch, int64_t m,
+                                     int64_t n, int64_t k, int64_t lda, int32_t trans_a,
+                                     int64_t ldb, int32_t trans_b, int32_t causal, int32_t cus,
+                                     uint32_t index) {
+  return estimated_us(shape_args(order, batch, m, n, k, lda, trans_a, ldb, trans_b, causal), index,
+                      cus);
 }
 
 // 1 where repops_matmul_grouped runs these products in one launch.

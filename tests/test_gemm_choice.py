@@ -1,15 +1,18 @@
 """The automatic choice of a product's launch, on the CPU: the rule is host
 arithmetic on sizes, strides and the number of compute units, so its routes can
 be checked without a device (the bits of every route are the GPU tests')."""
-import ctypes
+import math
 import os
 import re
 
 import pytest
 
+from perf import gemm_choice
+
 LIB = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))),
                    "paper_2502_19405_amd", "librepops.so")
-CUS = 256  # compute units of an MI355X
+TIMINGS = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))), "profiles",
+                       "gemm_choice_timings.csv")
 
 
 @pytest.fixture(scope="module")
@@ -21,15 +24,10 @@ def rp():
     return repops
 
 
-def choice(rp, m, n, k, batch=1, lda=None, ta=0, ldb=None, tb=0, causal=0, k_block=64, cus=CUS):
-    """(kind, index) of REPOPS_LAUNCH_AUTO; dense leading dimensions by default."""
-    i64, i32, u32 = ctypes.c_int64, ctypes.c_int32, ctypes.c_uint32
-    kind, index = u32(), u32()
-    rp.load().repops_internal_gemm_choice(
-        ctypes.byref(rp.Order(k_block=k_block).c()), i64(batch), i64(m), i64(n), i64(k),
-        i64(lda or (m if ta else k)), i32(ta), i64(ldb or (k if tb else n)), i32(tb), i32(causal),
-        i32(cus), ctypes.byref(kind), ctypes.byref(index))
-    return kind.value, index.value
+def choice(rp, m, n, k, **shape):
+    """(kind, index) of REPOPS_LAUNCH_AUTO; one product of dense rows by default."""
+    return gemm_choice.choice({"m": m, "n": n, "k": k, "batch": 1, "ta": 0, "tb": 0, "causal": 0,
+                               **shape})
 
 
 def tile(rp, index):
@@ -48,7 +46,7 @@ def tile(rp, index):
 @pytest.mark.parametrize("tb", [0, 1])
 def test_a_split_launch_stays_below_2_to_the_32_threads(rp, m, n, k, batch, ta, tb):
     """One workgroup per tile, and HIP refuses launches of 2^32 threads or more."""
-    kind, index = choice(rp, m, n, k, batch, ta=ta, tb=tb)
+    kind, index = choice(rp, m, n, k, batch=batch, ta=ta, tb=tb)
     assert kind == rp.LAUNCH_GEMM_MFMA
     bm, bn, waves = tile(rp, index)
     if waves:
@@ -68,3 +66,15 @@ def test_short_contractions_the_split_kernels_decline_keep_the_ring_form(rp, m, 
     if "batch" not in ld:  # few tiles: the register-staged form, as for other short k
         few = {"lda": 1 << 23, "ldb": 1 << 23}
         assert choice(rp, 2048, 2048, k, **few) == (rp.LAUNCH_GEMM_MFMA, 2)
+
+
+
+def test_the_choice_stays_near_the_fastest_entry():
+    """Over the recorded timings of every entry: a change of the estimates (or a new
+    file of timings) that sends products to slow entries fails here.  1.07 to 1.08
+    when this was written; a rule by size alone (64 x 64 tiles up to 2^20 outputs,
+    else the large tile) is at 3."""
+    loss = [us[gemm_choice.choice(s)[1]] / min(us.values())
+            for s, us in gemm_choice.recorded(TIMINGS)]
+    assert len(loss) > 400
+    assert math.exp(sum(math.log(x) for x in loss) / len(loss)) < 1.1

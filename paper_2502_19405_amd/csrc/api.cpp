@@ -118,8 +118,8 @@ struct GemmChoice {
 // Estimated time in us of matrix-core entry `index` on `cus` compute units; 0
 // where the automatic choice does not offer it: the split kernels for what they
 // take, 64-row tiles for products whose A is zero above its diagonal, for the
-// others the large tile, staged, register-staged or (short k) in its persistent
-// ring form.
+// others the large tile, staged, register-staged or (short k, more tiles than
+// compute units) in its persistent ring form.
 double estimated_us(const GemmArgs& g, uint32_t index, int cus) {
   const int split = static_cast<int>(index) - repops::gemm_mfma_first_split();
   if (split >= 0)
@@ -127,7 +127,7 @@ double estimated_us(const GemmArgs& g, uint32_t index, int cus) {
   const bool offered =
       g.causal == 2 ? index == 8
                     : index == 0 || index == 2 ||
-                          (index == 9 && g.k <= 256 && repops::gemm_mfma_ring_tiles(g, 9) > 0);
+                          (index == 9 && g.k <= 256 && repops::gemm_mfma_ring_tiles(g, 9) > cus);
   return offered ? repops::gemm_mfma_us(g, static_cast<int>(index), cus) : 0.0;
 }
 

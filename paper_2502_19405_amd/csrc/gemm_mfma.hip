@@ -1124,7 +1124,8 @@ int gemm_mfma_first_split() { return kMfmaCount; }
 // Measured as the split entries' estimates were: us per tile's k block and per
 // tile of one round of tiles over the compute units, for the staged (or ring)
 // kernel and for the register-staged one that takes its place at sizes or
-// alignments the staged kernel declines.  Entry 8 has three tiles per compute
+// alignments the staged kernel declines.  A round of staged tiles by itself has no
+// earlier tile's stores to wait behind.  Entry 8 has three tiles per compute
 // unit under way, so its rounds do not step.
 double gemm_mfma_us(const GemmArgs& g, int index, int cus) {
   const MfmaEntry& e = kMfma[index];
@@ -1145,8 +1146,10 @@ double gemm_mfma_us(const GemmArgs& g, int index, int cus) {
     const double load = tiles > cus ? part * tiles / cus : 1.0;
     return staged ? 2.8 + load * blocks * 4.0 : load * blocks * 7.2;
   }
-  const double cut = g.k % 64 != 0 ? 2.0 : 0.0;  // the short last block runs by itself
-  return staged ? 2.7 + per_cu * (4.0 * blocks + 6.2 + cut) : 4.0 + per_cu * (8.2 * blocks + 3.6);
+  if (!staged) return 4.0 + per_cu * (8.2 * blocks + 3.6);
+  // the short last block runs by itself
+  const double tile = g.k % 64 != 0 ? 8.2 : (per_cu > 1.0 ? 6.2 : 5.4);
+  return 2.7 + per_cu * (4.0 * blocks + tile);
 }
 
 void gemm_mfma_tile(int index, int* bm, int* bn, int* threads) {

@@ -68,7 +68,6 @@ def test_short_contractions_the_split_kernels_decline_keep_the_ring_form(rp, m, 
         assert choice(rp, 2048, 2048, k, **few) == (rp.LAUNCH_GEMM_MFMA, 2)
 
 
-
 def test_the_choice_stays_near_the_fastest_entry():
     """Over the recorded timings of every entry: a change of the estimates (or a new
     file of timings) that sends products to slow entries fails here.  1.07 to 1.08
@@ -78,3 +77,19 @@ def test_the_choice_stays_near_the_fastest_entry():
             for s, us in gemm_choice.recorded(TIMINGS)]
     assert len(loss) > 400
     assert math.exp(sum(math.log(x) for x in loss) / len(loss)) < 1.1
+
+
+@pytest.mark.parametrize("k", [64, 128, 192, 256])
+@pytest.mark.parametrize("tb", [0, 1])
+def test_the_ring_form_is_offered_only_where_it_runs(rp, k, tb):
+    """Up to one tile per compute unit entry 9's launch is entry 0's kernel, so one
+    computation has one price: entry 0's."""
+    for m in (128, 256, 384, 512, 768, 1024, 2048):
+        for n in (128, 512, 768, 1024, 2048, 4096, 8192):
+            for batch in (1, 4, 12, 32):
+                for causal in (0, 1) if m == n else (0,):
+                    t, u = m // 128, n // 128
+                    tiles = (t * (t + 1) // 2 if causal else t * u) * batch
+                    s = {"m": m, "n": n, "k": k, "batch": batch, "ta": 0, "tb": tb,
+                         "causal": causal}
+                    assert (gemm_choice.estimate(s, 9) > 0) == (tiles > gemm_choice.CUS), s

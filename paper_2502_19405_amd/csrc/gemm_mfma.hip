@@ -1142,9 +1142,11 @@ double gemm_mfma_us(const GemmArgs& g, int index, int cus) {
   if (index == 2) return 8.1 + per_cu * (5.8 * blocks + 3.2);
   if (index == 9) return 5.0 + per_cu * (4.1 * blocks + 3.0);
   if (g.causal == 2) {
-    const double part = 0.5 + 0.5 / static_cast<double>(tiles_m);
-    const double load = tiles > cus ? part * tiles / cus : 1.0;
-    return staged ? 2.8 + load * blocks * 4.0 : load * blocks * 7.2;
+    // Up to one tile per compute unit the longest tile bounds; beyond, the units'
+    // shares of tiles of unequal length.
+    const double r = tiles / cus;
+    if (staged) return 8.0 + 2.1 * blocks * (r <= 1.0 ? 1.0 : 0.9 + 0.66 * r);
+    return 6.0 + 6.3 * blocks * (r <= 1.0 ? 1.0 : 0.9 + 0.43 * r);
   }
   if (!staged) return 4.0 + per_cu * (8.2 * blocks + 3.6);
   // the short last block runs by itself

@@ -93,3 +93,18 @@ def test_the_ring_form_is_offered_only_where_it_runs(rp, k, tb):
                     s = {"m": m, "n": n, "k": k, "batch": batch, "ta": 0, "tb": tb,
                          "causal": causal}
                     assert (gemm_choice.estimate(s, 9) > 0) == (tiles > gemm_choice.CUS), s
+
+
+def test_no_recorded_product_is_slower_than_by_size():
+    """The estimates never do worse than the rule by size that they replaced: 64 x 64
+    tiles up to 2^20 outputs, register-staged slices for k <= 256, 64-row tiles where
+    A is zero above its diagonal, else the large tile.  (5%: the spread of a
+    recorded time.)"""
+    for s, us in gemm_choice.recorded(TIMINGS):
+        if s["m"] * s["n"] * s["batch"] <= 1 << 20:
+            by_size = 5
+        elif s["k"] <= 256:
+            by_size = 2
+        else:
+            by_size = 8 if s["causal"] == 2 else 0
+        assert us[gemm_choice.choice(s)[1]] <= 1.05 * us[by_size], s

@@ -1150,7 +1150,7 @@ double gemm_mfma_us(const GemmArgs& g, int index, int cus) {
   }
   if (!staged) return 4.0 + per_cu * (8.2 * blocks + 3.6);
   // the short last block runs by itself
-  const double tile = g.k % 64 != 0 ? 8.2 : (per_cu > 1.0 ? 6.2 : 5.4);
+  const double tile = g.k % 64 != 0 ? 8.2 : (per_cu > 1.0 ? 5.8 : 5.4);
   return 2.7 + per_cu * (4.0 * blocks + tile);
 }
 

@@ -525,19 +525,21 @@ __global__ __launch_bounds__(64 * KS, MINW) void gemm_split_kernel(GemmArgs g, u
 struct SplitEntry {
   GemmConfig cfg;
   int ks, slots;
-  // Time estimate in us, fitted to graph-replayed calls of 230 shapes (1 to 4096
-  // rows, 64 to 14336 columns and k, batched and causal ones; 7 to 16% mean
-  // deviation): start + the larger of one tile alone (`round` per round of
-  // blocks, `tile` for its first loads and its stores) and of the tiles a
-  // compute unit gets (`work` per full round and `tile`, each); and never less
-  // than the operands and outputs at `gbs`, what the tile's access pattern
-  // reaches from HBM.
-  float start, round, work, tile, gbs;
+  // Time estimate in us: start + the larger of one tile alone (`round` per round
+  // of blocks, `tile` for its first loads and its stores) and of the tiles a
+  // compute unit gets (`work` per full round, a partly filled one saving `fill`
+  // of what it leaves empty, and `tile`, each); and never less than the operands
+  // and outputs at `gbs`, what the tile's access pattern reaches from HBM.  The
+  // estimates are for ranking: over the 520 shapes of perf/gemm_choice.py those of
+  // the entries near the fastest are 6 (ring) to 52% (smallest tiles) off, most of
+  // them high together, and the chosen entry is 4% behind the fastest (geometric
+  // mean; more than 10% behind on 71 shapes).
+  float start, round, work, tile, fill, gbs;
   void (*kernel[4])(GemmArgs, uint32_t, uint32_t, uint32_t);  // [ta * 2 + tb]
 };
 
-#define REPOPS_SPLIT(NAME, R, MB, NB, KB, MI, KS, DEPTH, START, ROUND, WORK, TILE, GBS)  \
-  {{NAME, R * MB * MI, R * NB, kBlock}, KS, KS * KB, START, ROUND, WORK, TILE, GBS,      \
+#define REPOPS_SPLIT(NAME, R, MB, NB, KB, MI, KS, DEPTH, START, ROUND, WORK, TILE, FILL, GBS) \
+  {{NAME, R * MB * MI, R * NB, kBlock}, KS, KS * KB, START, ROUND, WORK, TILE, FILL, GBS, \
    {gemm_split_kernel<R, MB, NB, KB, MI, KS, DEPTH, 2, false, false>,                    \
     gemm_split_kernel<R, MB, NB, KB, MI, KS, DEPTH, 2, false, true>,                     \
     gemm_split_kernel<R, MB, NB, KB, MI, KS, DEPTH, 2, true, false>,                     \
@@ -546,15 +548,15 @@ struct SplitEntry {
 // Names: output tile x k block / waves, each with its own k blocks x k blocks per
 // instruction.
 const SplitEntry kSplit[] = {
-    REPOPS_SPLIT("32x64x64/k4", 32, 1, 2, 1, 1, 4, 2, 2.6f, 2.0f, 2.55f, 1.7f, 4700),
-    REPOPS_SPLIT("32x64x64/k8", 32, 1, 2, 1, 1, 8, 2, 2.6f, 0.3f, 5.1f, 2.2f, 5300),
-    REPOPS_SPLIT("64x64x64/k4", 32, 1, 2, 1, 2, 4, 2, 5.2f, 1.8f, 4.6f, 2.0f, 4500),
-    REPOPS_SPLIT("64x64x64/k8", 32, 1, 2, 1, 2, 8, 2, 2.6f, 2.6f, 9.2f, 3.0f, 4500),
-    REPOPS_SPLIT("16x64x64/k8", 16, 1, 4, 1, 1, 8, 4, 2.3f, 0.2f, 3.05f, 2.0f, 6600),
-    REPOPS_SPLIT("16x32x64/k8x2", 16, 1, 2, 2, 1, 8, 4, 2.2f, 2.5f, 3.4f, 2.2f, 5600),
-    REPOPS_SPLIT("16x16x64/k8x4", 16, 1, 1, 4, 1, 8, 4, 2.0f, 1.2f, 5.1f, 2.3f, 5000),
-    REPOPS_SPLIT("4x16x64/k8x4", 4, 1, 4, 4, 1, 8, 4, 2.6f, 1.4f, 3.3f, 1.0f, 6000),
-    REPOPS_SPLIT("16x16x64/k4", 4, 4, 4, 1, 1, 4, 4, 3.0f, 1.1f, 0.75f, 0.5f, 5200),
+    REPOPS_SPLIT("32x64x64/k4", 32, 1, 2, 1, 1, 4, 2, 2.6f, 2.0f, 2.55f, 1.7f, 0.7f, 4700),
+    REPOPS_SPLIT("32x64x64/k8", 32, 1, 2, 1, 1, 8, 2, 2.6f, 0.3f, 5.1f, 2.2f, 0.7f, 5300),
+    REPOPS_SPLIT("64x64x64/k4", 32, 1, 2, 1, 2, 4, 2, 5.2f, 1.8f, 4.6f, 2.0f, 0.6f, 4500),
+    REPOPS_SPLIT("64x64x64/k8", 32, 1, 2, 1, 2, 8, 2, 2.6f, 2.6f, 9.2f, 3.0f, 0.7f, 4500),
+    REPOPS_SPLIT("16x64x64/k8", 16, 1, 4, 1, 1, 8, 4, 2.3f, 0.2f, 3.05f, 2.0f, 0.7f, 6600),
+    REPOPS_SPLIT("16x32x64/k8x2", 16, 1, 2, 2, 1, 8, 4, 2.2f, 2.5f, 3.4f, 2.2f, 0.7f, 5600),
+    REPOPS_SPLIT("16x16x64/k8x4", 16, 1, 1, 4, 1, 8, 4, 2.0f, 1.2f, 5.1f, 2.3f, 0.7f, 5000),
+    REPOPS_SPLIT("4x16x64/k8x4", 4, 1, 4, 4, 1, 8, 4, 2.6f, 1.4f, 3.3f, 1.0f, 0.7f, 6000),
+    REPOPS_SPLIT("16x16x64/k4", 4, 4, 4, 1, 1, 4, 4, 3.0f, 1.1f, 0.75f, 0.5f, 0.7f, 5200),
 };
 constexpr int kSplitCount = sizeof(kSplit) / sizeof(kSplit[0]);
 
@@ -588,7 +590,7 @@ double gemm_split_us(const GemmArgs& g, int index, int cus) {
   if (g.causal == 2) part = 0.5 + 0.5 / std::ceil(blocks / e.slots);
   const double rounds = std::ceil(blocks / e.slots), per_cu = std::ceil(tiles / cus);
   // A partly filled round costs more than its share, and so does a short block.
-  double full = 0.7 * blocks / e.slots + 0.3 * rounds;
+  double full = e.fill * blocks / e.slots + (1.0 - e.fill) * rounds;
   if (blocks / e.slots < 0.3) full = 0.3;
   const double tile = e.tile + (g.k % kBlock != 0 ? 1.0 : 0.0);
   const double one = rounds * part * e.round + tile;

@@ -186,7 +186,7 @@ def check(path):
         taken[index] = taken.get(index, 0) + 1
         for i, t in us.items():
             e = estimate(s, i)
-            if e > 0:
+            if e > 0 and t < 1.5 * min(us.values()):  # where the estimate matters
                 off.setdefault(i, []).append(abs(e / t - 1))
     loss.sort(key=lambda x: -x[0])
     print("time of the chosen entry over the best one: geometric mean %.3f, above 1.1: %d of %d" % (

@@ -70,13 +70,13 @@ def test_short_contractions_the_split_kernels_decline_keep_the_ring_form(rp, m, 
 
 def test_the_choice_stays_near_the_fastest_entry():
     """Over the recorded timings of every entry: a change of the estimates (or a new
-    file of timings) that sends products to slow entries fails here.  1.07 to 1.08
-    when this was written; a rule by size alone (64 x 64 tiles up to 2^20 outputs,
+    file of timings) that sends products to slow entries fails here.  1.04 when this
+    was written; a rule by size alone (64 x 64 tiles up to 2^20 outputs,
     else the large tile) is at 3."""
     loss = [us[gemm_choice.choice(s)[1]] / min(us.values())
             for s, us in gemm_choice.recorded(TIMINGS)]
     assert len(loss) > 400
-    assert math.exp(sum(math.log(x) for x in loss) / len(loss)) < 1.1
+    assert math.exp(sum(math.log(x) for x in loss) / len(loss)) < 1.06
 
 
 @pytest.mark.parametrize("k", [64, 128, 192, 256])

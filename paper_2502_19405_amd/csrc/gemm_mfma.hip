@@ -1086,11 +1086,13 @@ const GemmConfig* gemm_mfma_config(int index) {
 bool gemm_mfma_staged_ok(const GemmArgs& g, int index) {
   const MfmaEntry& e = kMfma[index];
   if (!e.staged[1][0] || !operands_aligned(g) || (g.ta && g.m % 4 != 0) ||
-      (!g.tb && g.n % 4 != 0) || g.k / e.cfg.bk > INT32_MAX / 64 ||
-      g.k_block / e.cfg.bk > INT32_MAX)
+      (!g.tb && g.n % 4 != 0) || g.k / e.cfg.bk > INT32_MAX || g.k_block / e.cfg.bk > INT32_MAX)
     return false;
+  // the short last block's k indices, also those past the end, are ints
+  const bool cut = e.cut && g.k_block == 64;
+  if (cut && g.k > INT32_MAX - 64) return false;
   if (g.k % e.cfg.bk == 0) return true;
-  return e.cut && g.k_block == 64 && ((g.ta && !g.tb) || g.k % 4 == 0);
+  return cut && ((g.ta && !g.tb) || g.k % 4 == 0);
 }
 
 int device_cus() {

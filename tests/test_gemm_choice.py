@@ -108,3 +108,11 @@ def test_no_recorded_product_is_slower_than_by_size():
         else:
             by_size = 8 if s["causal"] == 2 else 0
         assert us[gemm_choice.choice(s)[1]] <= 1.05 * us[by_size], s
+
+
+@pytest.mark.parametrize("k", [(1 << 29) + 64, (1 << 30) + 64, (1 << 31) - 128])
+def test_the_staged_kernels_take_any_depth(rp, k):
+    """The register-staged kernel that would stand in needs twice the time a block."""
+    s = {"m": 256, "n": 256, "k": k, "batch": 1, "ta": 0, "tb": 0, "causal": 0}
+    short = {**s, "k": 1 << 20}
+    assert gemm_choice.estimate(s, 0) < 1.01 * k / (1 << 20) * gemm_choice.estimate(short, 0)

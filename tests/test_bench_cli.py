@@ -2,6 +2,7 @@
 the lookup of the headline kernel's HBM traffic from its counter summary."""
 import importlib.util
 import os
+import re
 import subprocess
 import sys
 
@@ -53,6 +54,16 @@ def test_traffic_comes_only_from_a_matching_counter_summary(bench, tmp_path, mon
     src.write_bytes(open(bench.KERNEL_SOURCES[0], "rb").read() + b"\n")
     monkeypatch.setattr(bench, "KERNEL_SOURCES", [str(src), *bench.KERNEL_SOURCES[1:]])
     assert bench.measured_traffic("auto", "dX") is None
+
+
+def test_the_kernel_hash_covers_the_kernel_and_its_choice(bench):
+    # every header of the kernel's own file, the tile mapping among them, and the
+    # files with the estimates that choose it
+    names = {os.path.basename(f) for f in bench.KERNEL_SOURCES}
+    src = open(next(f for f in bench.KERNEL_SOURCES if f.endswith("gemm_mfma.hip"))).read()
+    assert set(re.findall(r'#include "([^"]+)"', src)) <= names
+    assert {"api.cpp", "gemm_mfma.hip", "gemm_split.hip"} <= names
+    assert all(os.path.exists(f) for f in bench.KERNEL_SOURCES)
 
 
 def test_committed_counter_summary_parses(bench):

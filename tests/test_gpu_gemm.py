@@ -364,9 +364,9 @@ def test_negative_zero_partials_vanish_in_the_accumulator(rp, k, k_block):
 
 GROUP_CASES = [
     # (m, n, k, trans_a, trans_b, bias) per product
-    [(300, 260, 512, 1, 0, False), (520, 300, 128, 0, 1, True)],      # one launch, mixed layouts
+    [(300, 260, 512, 1, 0, False), (520, 300, 128, 0, 1, True)],      # mixed layouts
     [(96, 80, 256, 0, 0, True), (200, 132, 48, 1, 1, False), (64, 64, 1024, 0, 1, False)],
-    [(65, 70, 130, 0, 0, True), (33, 17, 64, 1, 0, False)],           # K % 16 != 0: one by one
+    [(65, 70, 130, 0, 0, True), (33, 17, 64, 1, 0, False)],           # unaligned rows
     [(0, 10, 16, 0, 0, False), (40, 44, 0, 0, 0, True), (70, 72, 96, 0, 0, False)],  # empty ones
 ]
 
@@ -375,8 +375,10 @@ GROUP_CASES = [
 @pytest.mark.parametrize("k_block,k_inner", [(64, 0), (0, 0), (64, 1)])
 def test_matmul_grouped_equals_single_products(rp, case, k_block, k_inner):
     """Every product of a grouped call has the bits of its own matmul call and
-    of the oracle -- in one launch (the staged tile) or one by one (other
-    shapes and orders)."""
+    of the oracle: with k_block 0 the first two groups run in one launch (the
+    staged tile); under the default order, where the time is estimated, groups as
+    small as these run one by one (large ones in one launch are in
+    test_gpu_split.py)."""
     g = inputs.rng(700 + case * 10 + k_block + k_inner)
     order = rp.Order(k_block=k_block, k_inner=k_inner)
     prods, wants, hosts = [], [], []

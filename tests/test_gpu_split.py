@@ -9,6 +9,8 @@ instruction; rows and columns around the tiles' edges; operands in all four
 layouts, with leading dimensions and origins that are 16-byte aligned and that
 are not.
 """
+import ctypes
+
 import numpy as np
 import pytest
 
@@ -129,6 +131,107 @@ def test_grouped_choice_keeps_the_bits(rp, tokens):
     assert_bits_equal(host(a)[r, c], oracle.matmul_at(dY, W, r, c, trans_b=True), "dX")
     r, c = inputs.sample_indices(tokens + 1, 256, 768, 3072)
     assert_bits_equal(host(b)[r, c], oracle.matmul_at(X, dY, r, c, trans_a=True), "dW")
+
+
+def in_one_launch(rp, prods):
+    """Whether the grouped call's rule runs these products in one launch here."""
+    import torch
+    descs = (rp.GemmDescT * len(prods))()
+    for d, (A, B, *_) in zip(descs, prods):
+        d.A, d.m, d.k, d.lda, d.trans_a = rp._mat(A, "A")
+        d.B, _, d.n, d.ldb, d.trans_b = rp._mat(B, "B")
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    return rp.load().repops_internal_grouped_choice(ctypes.byref(rp.Order().c()), len(prods),
+                                                    descs, cus) == 1
+
+
+# Ends of the contraction behind whole blocks: inside the first slice, behind one,
+# two and three whole slices, and just short of a block; then one short block alone
+@pytest.mark.parametrize("blocks,end", [(9, 4), (9, 20), (9, 36), (9, 52), (9, 60), (0, 36)])
+def test_grouped_short_last_blocks_in_every_layout(rp, blocks, end):
+    """One grouped launch (asserted) of all four layouts under the default order, rows
+    and columns ragged, with a bias and with a GELU input, K ending inside a block;
+    transposed A with plain B takes any K, the others multiples of 4."""
+    g = inputs.rng(6700 + 64 * blocks + end)
+    k = 64 * blocks + end
+    shapes = [(1301, 1412, k, 0, 0), (1143, 1337, k, 0, 1), (1204, 1500, k + 1, 1, 0),
+              (1108, 1237, k, 1, 1), (2052, 1028, k + 3, 1, 0)]
+    prods, hosts = [], []
+    for i, (m, n, kk, ta, tb) in enumerate(shapes):
+        A, B = inputs.normal(g, (kk, m) if ta else (m, kk)), inputs.normal(g, (n, kk) if tb else (kk, n))
+        bias = inputs.uniform(g, (n,), -0.1, 0.1) if i in (0, 2) else None
+        X = inputs.uniform(g, (m, n), -4.0, 4.0) if i in (1, 4) else None
+        hosts.append((A, B, bias, X))
+        prods.append((dev(A).t() if ta else dev(A), dev(B).t() if tb else dev(B),
+                      None if bias is None else dev(bias), None,
+                      *([] if X is None else [dev(X)])))
+    assert in_one_launch(rp, prods)
+    announce("grouped short last blocks", blocks, end)
+    outs = rp.matmul_grouped(prods)
+    simple = rp.Launch(rp.LAUNCH_GEMM_SIMPLE)
+    for i, (out, p, (A, B, bias, X)) in enumerate(zip(outs, prods, hosts)):
+        m, n, kk, ta, tb = shapes[i]
+        if X is None:
+            want = rp.matmul(p[0], p[1], p[2], launch=simple)
+        else:
+            want = rp.matmul_gelu_backward(p[0], p[1], p[4], launch=simple)
+        assert same_bits(out, want), shapes[i]
+        r, c = inputs.sample_indices(6700 + i, 200, m, n)
+        r, c = np.append(r, [0, m - 1, m - 1]), np.append(c, [n - 1, 0, n - 1])
+        ref = oracle.matmul_at(A, B, r, c, bias, trans_a=bool(ta), trans_b=bool(tb))
+        if X is not None:
+            ref = oracle.gelu_backward(np.ascontiguousarray(X[r, c]), ref)
+        assert_bits_equal(host(out)[r, c], ref, f"product {i} {shapes[i]}")
+
+
+@pytest.mark.parametrize("k", [16, 36, 70, 129, 515])
+def test_infinities_and_nan_near_the_cut(rp, k):
+    """Infinities and NaN in operands at the last k index, in the last whole slice and
+    at k 0: what lies past the end, and the values that stand in for it, must not
+    meet them (the products' own infinities and NaN must come out)."""
+    m, n = 68, 132
+    g = inputs.rng(8950 + k)
+    for where in sorted({0, k - 1, max(0, k // 16 * 16 - 1)}):
+        A, B = inputs.normal(g, (m, k)), inputs.normal(g, (k, n))
+        A[3, where], A[5, where], B[where, 7] = np.inf, np.nan, -np.inf
+        B[where, 9] = 0.0  # inf * 0
+        want = oracle.matmul(A, B)
+        assert np.isnan(want[5]).all() and np.isnan(want[3, 9]) and np.isfinite(want[4, 8])
+        for ta in (0, 1):
+            for tb in (0, 1):
+                a, b = operand(A, ta, 0), operand(B, tb, 0)
+                for name, launch in entries(rp):
+                    announce("infinities", k, where, ta, tb, name)
+                    got = host(rp.matmul(a, b, launch=launch))
+                    label = f"k {k} at {where} {ta}{tb} {name}"
+                    # which NaN a chain gives is not fixed: compare where, not its bits
+                    assert np.array_equal(np.isnan(got), np.isnan(want)), label
+                    assert_bits_equal(np.where(np.isnan(want), 0, got),
+                                      np.where(np.isnan(want), 0, want), label)
+
+
+@pytest.mark.parametrize("ta,tb", [(0, 0), (0, 1), (1, 0), (1, 1)])
+def test_leading_dimensions_over_2_to_the_22(rp, ta, tb):
+    """The split kernels' lane offsets take leading dimensions up to 2^22; past it
+    they decline, under AUTO and by name, and the bits stay."""
+    m, n, k = 9, 12, 20
+    ld = (1 << 22) + 4
+    g = inputs.rng(8970)
+    A, B = inputs.normal(g, (m, k)), inputs.normal(g, (k, n))
+    want = oracle.matmul(A, B)
+    import torch
+
+    def wide(a, transposed):
+        s = np.ascontiguousarray(a.T) if transposed else a
+        buf = torch.full(((s.shape[0] - 1) * ld + s.shape[1],), float("nan"), device="cuda:0")
+        v = buf.as_strided(s.shape, (ld, 1))
+        v.copy_(dev(s))
+        return v.t() if transposed else v
+
+    a, b = wide(A, ta), wide(B, tb)
+    for name, launch in entries(rp):
+        announce("wide leading dimensions", ta, tb, name)
+        assert_bits_equal(host(rp.matmul(a, b, launch=launch)), want, f"{ta}{tb} {name}")
 
 
 def test_products_of_more_tiles_than_one_launch_holds(rp):

@@ -199,10 +199,11 @@ repops_status_t repops_matmul_gelu_backward(const repops_order_t *order, int64_t
  * repops_matmul_grouped -- several independent products C_p = A_p.B_p (+ bias_p)
  * in one call, Section 3.2 (matrix multiplication) as for repops_matmul: each
  * product's outputs take exactly the bits repops_matmul gives for the same
- * arguments (repops_matmul_gelu_backward's where gelu_in is set).  The products run concurrently (one launch whose workgroups cover
- * every product's output tiles, the products with the longest contraction
- * first), so that products with few output tiles share the compute units:
- * the weight and input gradients of a linear layer are the intended use.
+ * arguments (repops_matmul_gelu_backward's where gelu_in is set).  Where it pays,
+ * the products run concurrently (one launch whose workgroups cover every
+ * product's output tiles, the products with the longest contraction first), so
+ * that products with few output tiles share the compute units: the weight and
+ * input gradients of a linear layer are the intended use.
  *   count   0 .. REPOPS_MAX_GROUP products; descs: host array of count entries
  *           (read during the call only; may be NULL when count = 0).
  *   each desc's fields as repops_matmul's arguments; gelu_in, ld_gelu_in: NULL
@@ -210,11 +211,15 @@ repops_status_t repops_matmul_gelu_backward(const repops_order_t *order, int64_t
  *           repops_matmul_gelu_backward (then bias must be NULL).
  *   No C_p may overlap its own operands or any other product's A, B, bias,
  *   gelu_in or C (REPOPS_ERR_ALIAS).
- *   launch  NULL or AUTO.  When every nonempty product has K > 0, K and k_block
- *           multiples of 16, 16-byte aligned rows and the fused order, one
- *           launch of the 128 x 128 matrix-core tile runs them all; otherwise the
- *           products run one after another with repops_matmul's automatic
- *           launch (the same bits either way).
+ *   launch  NULL or AUTO.  One launch of the 128 x 128 matrix-core tile runs all
+ *           products where the order is fused, every nonempty product has K > 0,
+ *           16-byte aligned rows (operands stored along rows with a multiple of 4
+ *           of them) and whole 16-deep k slices -- or, with k_block 64, any K
+ *           whose operands stored along k have a multiple of 4 -- and, with
+ *           k_block 64, the one launch is not estimated slower than the products'
+ *           own (few tokens, whose tiles leave most compute units idle).
+ *           Otherwise the products run one after another with repops_matmul's
+ *           automatic launch (the same bits either way).
  */
 typedef struct repops_gemm_desc {
     int64_t m, n, k;

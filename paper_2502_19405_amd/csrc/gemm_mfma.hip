@@ -982,8 +982,8 @@ struct MfmaEntry {
   int threads;
   bool cut;  // the staged kernels run a short last block (StagedTile::CUT)
   void (*kernel[4])(GemmArgs, int64_t, int64_t, int64_t, int);  // [ta * 2 + tb]
-  // staged variant of the same tile shape (nullptr: none); needs K % 16 == 0
-  // and 16-byte aligned rows.  [0]: for products with no scale, bias or GELU
+  // staged variant of the same tile shape (nullptr: none), for the products that
+  // gemm_mfma_staged_ok accepts.  [0]: for products with no scale, bias or GELU
   // array; [1]: for the others (the specialised interior stores)
   void (*staged[2][4])(GemmArgs, int64_t, int64_t, int64_t, int);
   // persistent form of the staged tile with the ring running across tiles

@@ -24,13 +24,14 @@
 //
 // What bounds it: few outputs, the latency of one block (64 matrix steps), its
 // loads and the launch; few rows, the reading of B from HBM; many outputs, the
-// matrix units (0.55 to 0.7 of them busy: a round's partials pass through LDS
-// behind a barrier, and a 32 x 64 tile reads three times the operand bytes per
-// step of the 128 x 128 tile, which is why the large tile stays the better one
-// from about one tile per compute unit on).  Measured, graph-replayed, against
-// the one-wave walk (64 x 64 tiles): 256^3 18.2 -> 3.7 us, 512^3 31.6 -> 6.3,
-// 1000 x 999 x 1001 75 -> 25, 4 x 14336 outputs with k 4096 283 -> 38.5 (6.1 TB/s
-// of B), 128 x 3072 with k 768 44 -> 11.4, 128 x 768 with k 3072 161 -> 13.5.
+// matrix units (counted busy 0.70 of the time at 4096 x 768 outputs and k 3072,
+// 0.41 at 1000 x 999 x 1001: a round's partials pass through LDS behind a barrier,
+// and a 32 x 64 tile reads three times the operand bytes per step of the 128 x 128
+// tile, which is why the large tile stays the better one from about one tile per
+// compute unit on).  Measured, graph-replayed, against the one-wave walk (64 x 64
+// tiles): 256^3 18.2 -> 3.7 us, 512^3 31.6 -> 6.3, 1000 x 999 x 1001 75 -> 25,
+// 4 x 14336 outputs with k 4096 283 -> 38.5 (6.1 TB/s of B), 128 x 3072 with k 768
+// 44 -> 11.4, 128 x 768 with k 3072 161 -> 13.5.
 //
 // The matrix instruction is one of the single-term kinds
 //   R = 32: v_mfma_f32_32x32x1_2b    two   32 x 32 blocks, 16 passes
@@ -505,8 +506,9 @@ __global__ __launch_bounds__(64 * KS, MINW) void gemm_split_kernel(GemmArgs g, u
                                                                    uint32_t ntiles) {
   using T = SplitTile<R, MB, NB, KB, MI, KS, DEPTH, TA, TB>;
   __shared__ typename T::Smem sm;
-  // Tiles in panels of four tile rows, a contiguous share of them per XCD
-  // (workgroups are dealt round-robin over eight).
+  // tile_coords' mapping in 32-bit arithmetic (gemm_split_ok bounds the tiles):
+  // panels of four tile rows, a contiguous share of them per XCD.  Lower-triangle
+  // products launch every tile; those above the diagonal return.
   uint32_t t = blockIdx.x;
   if (ntiles % 8 == 0) t = (t % 8) * (ntiles / 8) + t / 8;
   const uint32_t per = tiles_m * tiles_n;

@@ -10,9 +10,9 @@
 //
 // Schedule: one lane per leaf chunk (the chunk's blocks in sequence); then
 // the tree level by level, pairs hashed and an odd last node carried up
-// unchanged (which reproduces RFC 6962's split): one launch per level while a
-// level is wider than 65536 nodes, then eight levels per launch from LDS, the
-// last of which writes the root as 32 bytes.  A level costs at least one
+// unchanged (which reproduces RFC 6962's split): one launch per level, eight
+// levels per launch from LDS between 65536 and 16384 nodes, and the last 256 nodes
+// in one workgroup, which writes the root as 32 bytes.  A level costs at least one
 // two-block hash of latency, so a tensor's commitment has a floor of about that
 // times the tree depth; wide levels and the leaves are integer-ALU bound.
 //
@@ -52,9 +52,14 @@ constexpr int kSplitLeaves = 128;  // leaves of a workgroup with two waves a lea
 // 47.2 us just above this line, two waves a leaf 38.9 us at it).
 constexpr uint64_t kFewLeaves = 256 * kSplitLeaves;
 constexpr int kTopThreads = 256;   // two for each of the 128 pairs
-// Nodes up to which a level is reduced in slices: at most one workgroup per
-// compute unit, whose SIMDs then hold one wave each.  A wider level fills the
-// SIMDs by itself and takes a launch of its own.
+// Levels of more nodes than the first and at most the second are reduced in
+// slices, at most one workgroup per compute unit, whose SIMDs then hold one wave
+// each.  A wider level fills the SIMDs by itself and takes a launch of its own; so
+// does a narrower one, whose launch costs less than a level of slices (whole
+// commitments of 64-byte leaves, slices against launches: 2000 leaves 76.9 and
+// 69.7 us, 8192 87.8 and 88.1, 16384 93.2 and 89.7, 24000 97.6 and 97.3, 32768
+// 97.2 and 98.1, 65536 99.7 and 105.9).
+constexpr uint64_t kLevelNodes = 64 * kTopNodes;
 constexpr uint64_t kSliceNodes = 256 * kTopNodes;
 
 __device__ __forceinline__ uint32_t rotr(uint32_t x, int n) { return (x >> n) | (x << (32 - n)); }
@@ -248,7 +253,8 @@ __global__ __launch_bounds__(256) void leaf_kernel(const uint8_t* data, uint64_t
 // of the threads make the message schedule (a third of the instructions) 16 words
 // ahead of the rounds, as in the tree's slices below.  chunk is a multiple of 64
 // and data 16-byte aligned.  32768 leaves of 1 KiB 47.2 -> 38.9 us; the whole
-// commitment of 48 leaves 81 -> 70 us, of 2304 119 -> 112, of 32768 141 -> 129.
+// commitment, its tree as below, of 48 leaves 81 -> 70 us, of 2000 113 -> 99, of
+// 32768 139 -> 127.
 __global__ __launch_bounds__(2 * kSplitLeaves) void leaf_split_kernel(const uint8_t* data,
                                                                       uint64_t nbytes,
                                                                       uint32_t chunk,
@@ -522,7 +528,7 @@ hipError_t launch_commit(const uint8_t* data, uint64_t nbytes, uint32_t chunk, u
   hipError_t e = hipGetLastError();
   uint64_t n = leaves;
   while (e == hipSuccess && n > static_cast<uint64_t>(kTopNodes)) {
-    if (n > kSliceNodes) {
+    if (n > kSliceNodes || n <= kLevelNodes) {
       hipLaunchKernelGGL(node_kernel, dim3(grid_for((n + 1) / 2, 256)), dim3(256), 0, s, a, n, b);
       n = (n + 1) / 2;
     } else {

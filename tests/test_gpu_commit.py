@@ -78,12 +78,13 @@ def test_commit_llama_mlp_weight(rp):
     assert got == oracle.commit(W, 1024)
 
 
-@pytest.mark.parametrize("leaves", [127, 128, 129, 256, 257, 384, 32768, 32769, 65536, 65537])
+@pytest.mark.parametrize("leaves", [127, 128, 129, 256, 257, 384, 512, 513, 16384, 16385,
+                                    16640, 32768, 32769, 65536, 65537])
 @pytest.mark.parametrize("short", [0, 3])
 def test_commit_launch_edges(rp, leaves, short):
     """Leaf counts where the launches change: 128 leaves to a workgroup of two
-    waves a leaf, up to 32768 of them; 256 nodes to a tree slice, up to 65536 in
-    slices; with a whole and a short last chunk."""
+    waves a leaf, up to 32768 of them; 256 nodes to a tree slice, over 16384 and up
+    to 65536 of them in slices; with a whole and a short last chunk."""
     data = inputs.rng(954 + leaves).integers(0, 256, leaves * 64 - short).astype(np.uint8)
     announce("commit launches", leaves, short)
     assert gpu_commit(rp, data, 64) == oracle.commit(data, 64)
